@@ -217,6 +217,24 @@ __device__ inline double wave_max(double v) {
     return v;
 }
 
+// Sum (slot 7: maximum) of the threads' accumulators over a workgroup of
+// kReduceThreads threads; thread k < kReduceSlots returns slot k.
+__device__ inline double block_sums(const double (&acc)[kReduceSlots]) {
+    __shared__ double sm[kReduceSlots][kReduceThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < kReduceSlots; ++k) {
+        const double v = (k == 7) ? wave_max(acc[k]) : wave_sum(acc[k]);
+        if (lane == 0) sm[k][wave] = v;
+    }
+    __syncthreads();
+    const int k = (int)threadIdx.x;
+    if (k >= kReduceSlots) return 0.0;
+    double v = sm[k][0];
+    for (int w = 1; w < kReduceThreads / 64; ++w) v = (k == 7) ? fmax(v, sm[k][w]) : v + sm[k][w];
+    return v;
+}
+
 template <typename S>
 __global__ void __launch_bounds__(kReduceThreads)
 reduce_kernel(const S *__restrict__ A, const uint8_t *__restrict__ flags, double *__restrict__ snap, int have_prev,
@@ -254,32 +272,31 @@ reduce_kernel(const S *__restrict__ A, const uint8_t *__restrict__ flags, double
         acc[8] += 0.5 * r * u2;
         acc[9] += 1.0;
     }
-    __shared__ double sm[kReduceSlots][kReduceThreads / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < kReduceSlots; ++k) {
-        const double v = (k == 7) ? wave_max(acc[k]) : wave_sum(acc[k]);
-        if (lane == 0) sm[k][wave] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < kReduceSlots) {
-        const int k = threadIdx.x;
-        double v = sm[k][0];
-        for (int w = 1; w < kReduceThreads / 64; ++w) v = (k == 7) ? fmax(v, sm[k][w]) : v + sm[k][w];
-        partials[(int64_t)blockIdx.x * kReduceSlots + k] = v;
-    }
+    const double v = block_sums(acc);
+    if (threadIdx.x < kReduceSlots) partials[(int64_t)blockIdx.x * kReduceSlots + threadIdx.x] = v;
 }
 
-__global__ void __launch_bounds__(64)
-reduce_final_kernel(const double *__restrict__ partials, int nblocks, double *__restrict__ out) {
-    const int k = threadIdx.x;
-    if (k >= kReduceSlots) return;
-    double v = 0.0;
-    for (int b = 0; b < nblocks; ++b) {
-        const double x = partials[(int64_t)b * kReduceSlots + k];
-        v = (k == 7) ? fmax(v, x) : v + x;
+// Sums of the block partials in a fixed order by one workgroup: thread t
+// takes the blocks t, t + 256, ..., then the wave and workgroup sums; thread k
+// returns slot k.  (A single thread per slot walking all blocks is a chain of
+// up to 1024 dependent additions behind their loads: 183 us for 1024 blocks,
+// against 6 us here.)
+__device__ inline double sum_partials(const double *__restrict__ partials, int nblocks) {
+    double acc[kReduceSlots];
+#pragma unroll
+    for (int k = 0; k < kReduceSlots; ++k) acc[k] = 0.0;
+    for (int b = threadIdx.x; b < nblocks; b += kReduceThreads) {
+        const double *x = partials + (int64_t)b * kReduceSlots;
+#pragma unroll
+        for (int k = 0; k < kReduceSlots; ++k) acc[k] = (k == 7) ? fmax(acc[k], x[k]) : acc[k] + x[k];
     }
-    out[k] = v;
+    return block_sums(acc);
+}
+
+__global__ void __launch_bounds__(kReduceThreads)
+reduce_final_kernel(const double *__restrict__ partials, int nblocks, double *__restrict__ out) {
+    const double v = sum_partials(partials, nblocks);
+    if (threadIdx.x < kReduceSlots) out[threadIdx.x] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -319,18 +336,12 @@ static hipError_t scratch_address(double **out) {
 // Fixed-order sums of the partials (as reduce_final_kernel), then the eight
 // outputs of clbm_reduce: fluid mass, momentum, residual, non-finite count,
 // max |u|, kinetic energy.
-__global__ void __launch_bounds__(64)
-reduce_finish_kernel(const double *__restrict__ partials, int nblocks, int have_prev, double *__restrict__ sums,
-                     double *__restrict__ out) {
-    const int k = threadIdx.x;
-    if (k < kReduceSlots) {
-        double v = 0.0;
-        for (int b = 0; b < nblocks; ++b) {
-            const double x = partials[(int64_t)b * kReduceSlots + k];
-            v = (k == 7) ? fmax(v, x) : v + x;
-        }
-        sums[k] = v;
-    }
+__global__ void __launch_bounds__(kReduceThreads)
+reduce_finish_kernel(const double *__restrict__ partials, int nblocks, int have_prev, double *__restrict__ out) {
+    __shared__ double sums[kReduceSlots];
+    const int k = (int)threadIdx.x;
+    const double v = sum_partials(partials, nblocks);
+    if (k < kReduceSlots) sums[k] = v;
     __syncthreads();
     if (k == 0) {
         out[0] = sums[9] + sums[0];
@@ -351,13 +362,12 @@ static hipError_t launch_reduce_noalloc_t(const void *A, const uint8_t *flags, d
     double *ptr = nullptr;
     hipError_t e = scratch_address(&ptr);
     if (e != hipSuccess) return e;
-    double *sums = ptr + (size_t)kNoAllocMaxBlocks * kReduceSlots;
     hipLaunchKernelGGL((reduce_kernel<S>), dim3(nblocks), dim3(kReduceThreads), 0, st, (const S *)A, flags, snap,
                        have_prev, g, F[0], F[1], F[2], ptr);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_finish_kernel, dim3(1), dim3(64), 0, st, (const double *)ptr, nblocks,
-                       snap && have_prev ? 1 : 0, sums, out);
+    hipLaunchKernelGGL(reduce_finish_kernel, dim3(1), dim3(kReduceThreads), 0, st, (const double *)ptr, nblocks,
+                       snap && have_prev ? 1 : 0, out);
     return hipGetLastError();
 }
 
@@ -604,7 +614,7 @@ static hipError_t launch_reduce_t(const void *A, const uint8_t *flags, double *s
                        have_prev, g, F[0], F[1], F[2], partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(64), 0, st, (const double *)partials, nblocks, out);
+    hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(kReduceThreads), 0, st, (const double *)partials, nblocks, out);
     return hipGetLastError();
 }
 
