@@ -290,8 +290,8 @@ clbm_status clbm_state(clbm_lattice *h, int *buffer_index, int64_t *steps_done);
 typedef struct {
     int32_t bx, by;      /* threads per block along x and y: bx*by at most 512 (FP32/FP16
                             storage) or 256 (FP64); whole 64-lane waves run fastest (row
-                            layout: bx a multiple of 64 takes the fast kernel, other widths a
-                            kernel that applies the full wall rule on every lane) */
+                            layout: a block takes bx*by, rounded up to whole waves,
+                            consecutive nodes or runs of 64) */
     int32_t xcd_remap;   /* 1: workgroup b takes tile (b mod 8)*(B/8) + b/8, so each of the
                             eight XCDs sweeps a contiguous slab of the lattice (both launch
                             forms) */

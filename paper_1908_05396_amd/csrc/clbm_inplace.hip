@@ -289,25 +289,24 @@ aa_any_kernel(S *__restrict__ A, Geom g, Relax<T> p, LaunchGrid L) {
 
 template <typename S, typename T, bool Forced, int Route>
 static hipError_t aa_pair_rows_f(void *A, const Geom &g, const Relax<T> &p, const StepLaunch &c, hipStream_t st) {
-    const RowLaunch L = row_launch(g, c.bx, c.by, c.xcd_remap);
-    const dim3 block(c.bx, c.by);
-    RowGrid all = L.inner;      // the even step: every row, r = ri
-    all.rows = (uint32_t)g.ny * (uint32_t)g.nz;
-    const uint32_t nb = all.gx * ((all.rows + c.by - 1) / c.by);
-    all.aligned = nb & ~7u;
+    const int threads = c.bx * c.by;
+    RowGrid R;
+    uint32_t blocks = all_rows(g, threads, c.xcd_remap, R);
     Relax<T> q = p;             // the odd step is the next collision
     q.step = p.step + 1u;
-    hipLaunchKernelGGL((aa_even_rows_kernel<S, T, Forced, Route>), dim3(nb), block, 0, st, (S *)A, g, p, all);
+    hipLaunchKernelGGL((aa_even_rows_kernel<S, T, Forced, Route>), dim3(blocks), dim3(threads), 0, st, (S *)A, g, p, R);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (L.inner.rows > 0) {
-        hipLaunchKernelGGL((aa_odd_rows_kernel<S, T, Forced, Route>), dim3(L.inner_blocks), block, 0, st, (S *)A, g,
-                           q, L.inner);
+    blocks = inner_rows(g, threads, c.xcd_remap, R);
+    if (blocks > 0) {
+        hipLaunchKernelGGL((aa_odd_rows_kernel<S, T, Forced, Route>), dim3(blocks), dim3(threads), 0, st, (S *)A, g, q,
+                           R);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((aa_odd_rows_face_kernel<S, T, Forced, Route>), dim3(L.face_blocks), block, 0, st, (S *)A, g,
-                       q, L.face);
+    blocks = face_rows(g, threads, R);
+    hipLaunchKernelGGL((aa_odd_rows_face_kernel<S, T, Forced, Route>), dim3(blocks), dim3(threads), 0, st, (S *)A, g, q,
+                       R);
     return hipGetLastError();
 }
 

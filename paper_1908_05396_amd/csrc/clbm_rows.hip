@@ -7,52 +7,117 @@
 // over the whole buffer, which keeps the DRAM page and bank traffic of
 // neighbouring waves together.
 //
-//   stream_collide_rows       rows off the y and z faces.  Each wave covers
-//                             64 consecutive x of one row (blockDim.x a
-//                             multiple of 64), so the source of direction a
-//                             is a uniform address plus the lane's x: one
-//                             scalar base per load and store, one shared
-//                             lane offset; only the lanes on an x face take a
-//                             wall rule.
-//   stream_collide_rows_face  the rows on a y or z face (about 6/L of an L^3
-//                             lattice), launched after the first kernel: per
-//                             direction, uniformly, a source row inside,
-//                             wrapped, or a ghost (bounce-back).  Keeping them
-//                             apart keeps the first kernel's scalar registers
-//                             low enough for eight waves per SIMD.
-//   stream_collide_any        any block shape: the full rule on every lane
-//                             (narrow lattices).
+//   stream_collide_flat   one thread per node, 64 consecutive nodes per wave,
+//                         per-lane source addresses: no idle lanes at any
+//                         width, no second launch or second round of loads for
+//                         the faces.
+//   stream_collide_rows   large FP32 lattices: each wave covers 64 consecutive
+//                         x of one row, so a direction's source is a uniform
+//                         address plus the lane's x; rows on a y or z face
+//                         take the wall rule by scalar selects, the lanes of
+//                         the x faces by a second group of loads.
 #include "clbm_rows.hpp"
 
 namespace clbm {
 
 namespace {
 
-// Pull along e_a with the full wall logic (Eq. cascaded streaming with the
-// rules of Sec. 4), in either layout: periodic wrap, half-way bounce-back,
-// moving lid.  a = 0 returns the node's own rest population.
-template <typename S, typename T>
-__device__ inline T pull_any(const S *__restrict__ A, const Geom &g, const Relax<T> &p, int a, int x, int y, int z) {
-    int sx = x - cx(a), sy = y - cy(a), sz = z - cz(a);
-    const bool in_lid = ghost_in_lid(g, sx, sy, sz);
-    bool wall = false;
-    if (sx < 0 || sx >= g.nx) { if (g.px) sx = sx < 0 ? sx + g.nx : sx - g.nx; else wall = true; }
-    if (sy < 0 || sy >= g.ny) { if (g.py) sy = sy < 0 ? sy + g.ny : sy - g.ny; else wall = true; }
-    if (sz < 0 || sz >= g.nz) { if (g.pz) sz = sz < 0 ? sz + g.nz : sz - g.nz; else wall = true; }
-    if (!wall) return (T)Conv<S, T>::load(A[elem(g, a, sx, sy, sz)]);
-    return wall_value<T>((T)Conv<S, T>::load(A[elem(g, opp(a), x, y, z)]), p, a, in_lid);
-}
-
-__device__ inline void tile_of(const LaunchGrid &L, uint32_t &tx, uint32_t &ty, int &z) {
-    uint32_t b = blockIdx.x;
-    if (L.remap && b < L.aligned) b = (b & 7u) * (L.aligned >> 3) + (b >> 3);
-    tx = b % L.gx;
-    b /= L.gx;
-    ty = b % L.gy;
-    z = (int)(b / L.gy);
+// Pull gather of 64 consecutive nodes with the full wall logic (Eq. cascaded
+// streaming with the rules of Sec. 4) on every lane: periodic wrap, half-way
+// bounce-back, moving lid.  Which value a direction reads - the source's, or
+// the node's own opposite population beyond a wall - is a select on its
+// address, so the 19 loads go out together and the wave waits for memory once;
+// the lid terms are added afterwards, in waves that touch the lid.
+//
+// `own` is the byte offset from A of the node's own row group plus its x, and
+// every source lies within 32 bits of it: loads go through one descriptor
+// that starts K = layer + row + one value before A (no access falls before A),
+// which keeps the lane offsets positive.  Far: the lattice itself is larger;
+// lanes that pull across a periodic z face then address in 64 bits.
+//
+// Waves without a face node could use one lane offset and 19 scalar ones.
+// Their loads then issue back to back, which the memory serves worse than
+// loads a few instructions apart: 200 x 190 x 220 FP32 304 us per step with
+// that path against 250 without, 256^3 FP16 233 against 227; not kept.
+template <typename S, typename T, int LdAux, bool Far>
+__device__ inline void gather_flat(const S *__restrict__ A, uint32_t own, const Geom &g, const Relax<T> &p, int x,
+                                   int y, int z, T (&d)[Q]) {
+    constexpr uint32_t es = sizeof(S);
+    const uint32_t run = (uint32_t)g.nx * es, row = Q * run, layer = row * (uint32_t)g.ny, K = layer + row + es;
+    const bool lo[3] = {x == 0, y == 0, z == 0};
+    const bool hi[3] = {x == g.nx - 1, y == g.ny - 1, z == g.nz - 1};
+    const bool per[3] = {g.px != 0, g.py != 0, g.pz != 0};
+    // per axis, index c + 1 for c = -1, 0, +1: byte distance to the (wrapped)
+    // source (Far: lanes wrapping in z read their own layer here and are redone below)
+    const uint32_t wrap = Far ? layer : layer * (uint32_t)g.nz;
+    const uint32_t dx[3] = {hi[0] ? es - run : es, 0u, lo[0] ? run - es : 0u - es};
+    const uint32_t dy[3] = {hi[1] ? row - layer : row, 0u, lo[1] ? layer - row : 0u - row};
+    const uint32_t dz[3] = {hi[2] ? layer - wrap : layer, 0u, lo[2] ? wrap - layer : 0u - layer};
+    auto ghost = [&](int axis, int c) { return c != 0 && !per[axis] && (c == 1 ? lo[axis] : hi[axis]); };
+    const __amdgpu_buffer_rsrc_t rsrc = row_rsrc((const char *)A - K, 0xFFFFFFFFu);
+    const uint32_t self = own + K;
+#pragma unroll
+    for (int a = 0; a < Q; ++a) {
+        const bool wall = ghost(0, cx(a)) | ghost(1, cy(a)) | ghost(2, cz(a));
+        const uint32_t src = self + dx[cx(a) + 1] + dy[cy(a) + 1] + dz[cz(a) + 1];
+        d[a] = (T)RawBits<S>::template load<LdAux>(rsrc, wall ? self + (uint32_t)(opp(a) - a) * run : src,
+                                                   (uint32_t)a * run);
+    }
+    const int m = g.lid_mask;
+    auto lid = [&](int axis, int c) {
+        return c != 0 && (c == 1 ? ((m >> (2 * axis)) & 1) && lo[axis] : ((m >> (2 * axis + 1)) & 1) && hi[axis]);
+    };
+    const bool any = lid(0, 1) | lid(0, -1) | lid(1, 1) | lid(1, -1) | lid(2, 1) | lid(2, -1);
+    if (__builtin_amdgcn_ballot_w64(any) != 0) {
+#pragma unroll
+        for (int a = 1; a < Q; ++a)
+            d[a] = wall_value<T>(d[a], p, a, lid(0, cx(a)) | lid(1, cy(a)) | lid(2, cz(a)));
+    }
+    if constexpr (Far) {
+        if (per[2] && (lo[2] || hi[2])) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a) {
+                if (cz(a) == 0 || !(cz(a) == 1 ? lo[2] : hi[2]) || ghost(0, cx(a)) || ghost(1, cy(a))) continue;
+                const int64_t to = (int64_t)(int32_t)(dx[cx(a) + 1] + dy[cy(a) + 1]) + (int64_t)a * run +
+                                   cz(a) * (int64_t)(g.nz - 1) * (int64_t)layer;
+                d[a] = (T)Conv<S, T>::load(*(const S *)((const char *)A + own + to));
+            }
+        }
+    }
 }
 
 }  // namespace
+
+// One thread per node, 64 consecutive nodes (x fastest, across rows and
+// layers) per wave, so no lane is idle at any width.
+//
+// Bound: HBM for FP32 and FP64 (256^3: 448 us per step, 5.7 TB/s, and 880 us,
+// 5.8 TB/s, against 6.55 of a copy; the kernel with one wave per run of a row
+// and the faces in a second launch took 464 and 904), arithmetic for FP16
+// (227 against 271 us; the hash of the stochastic rounding and the relaxation
+// rate, 61 VGPRs and eight waves per SIMD), latency of one pass below about
+// 10^5 nodes (64^3 FP32: 8.0 against 18.6 us, 48^3 5.0 against 9.3).  Rows that
+// are not whole cache lines gain most, since the lines two runs share meet in
+// one workgroup: 200 x 190 x 220 FP32 250 against 375 us.
+template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route, bool Far>
+__global__ void __launch_bounds__(MaxThreads<T>::value)
+stream_collide_flat_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, FlatGrid L) {
+    uint32_t b = blockIdx.x;
+    if (L.remap && b < L.aligned) b = (b & 7u) * (L.aligned >> 3) + (b >> 3);
+    const uint32_t i = b * blockDim.x + threadIdx.x;
+    if (i >= (uint32_t)g.n) return;
+    const uint32_t r = L.by_nx.quotient(i), zr = L.by_ny.quotient(r);
+    const int x = (int)(i - r * (uint32_t)g.nx), y = (int)(r - zr * (uint32_t)g.ny), z = (int)zr;
+    const uint32_t run = (uint32_t)g.nx * (uint32_t)sizeof(S);
+    // Far: offsets count from the layer of the wave's first node
+    const uint32_t r0 = Far ? __builtin_amdgcn_readfirstlane(zr) * (uint32_t)g.ny : 0u;
+    const uint32_t own = (r - r0) * (Q * run) + (uint32_t)x * (uint32_t)sizeof(S);
+    T d[Q];
+    gather_flat<S, T, LdAux, Far>(A + (int64_t)r0 * g.row, own, g, p, x, y, z, d);
+    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
+    row_store_at<S, T, StAux>(row_rsrc(B + (int64_t)r0 * g.row, 0xFFFFFFFFu), own, run, d, p.sr != 0,
+                              sr_base(i, p.step));
+}
 
 template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
@@ -60,54 +125,53 @@ stream_collide_rows_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, R
     int x;
     uint32_t ri;
     if (!row_of(R, x, ri) || x >= g.nx) return;
-    int y, z;
-    inner_row(g, ri, y, z);
-    row_step<S, T, Forced, LdAux, StAux, Route, false, XGroupRows<S>::value>(A, B, g, p, x, y, z, p.step);
-}
-
-template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route>
-__global__ void __launch_bounds__(MaxThreads<T>::value)
-stream_collide_rows_face_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, RowGrid R) {
-    int x;
-    uint32_t ri;
-    if (!row_of(R, x, ri) || x >= g.nx) return;
-    int y, z;
-    face_row(g, R, ri, y, z);
-    row_step<S, T, Forced, LdAux, StAux, Route, true, XGroupRows<S>::value>(A, B, g, p, x, y, z, p.step);
-}
-
-template <typename S, typename T, bool Forced, int Route>
-__global__ void __launch_bounds__(MaxThreads<T>::value)
-stream_collide_any_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, LaunchGrid L) {
-    uint32_t tx, ty;
-    int z;
-    tile_of(L, tx, ty, z);
-    const int x = (int)(tx * blockDim.x + threadIdx.x);
-    const int y = (int)(ty * blockDim.y + threadIdx.y);
-    if (y >= g.ny || x >= g.nx) return;
+    const int y = (int)(ri % (uint32_t)g.ny), z = (int)(ri / (uint32_t)g.ny);
     T d[Q];
-#pragma unroll
-    for (int a = 0; a < Q; ++a) d[a] = pull_any<S, T>(A, g, p, a, x, y, z);
+    if (y >= 1 && y <= g.ny - 2 && z >= 1 && z <= g.nz - 2)
+        row_gather<S, T, LdAux, false, false, XGroupRows<S>::value>(A, g, p, x, y, z, d);
+    else
+        row_gather<S, T, LdAux, true, false, XGroupRows<S>::value>(A, g, p, x, y, z, d);
     collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    round_state<S, T>(d, p, (uint32_t)x + (uint32_t)g.nx * ((uint32_t)y + (uint32_t)g.ny * (uint32_t)z), p.step);
-#pragma unroll
-    for (int a = 0; a < Q; ++a) B[elem(g, a, x, y, z)] = Conv<S, T>::store(d[a]);
+    const uint32_t node = (uint32_t)x + (uint32_t)g.nx * ri;
+    row_store<S, T, StAux>(B, g, x, y, z, d, p.sr != 0, sr_base(node, p.step));
 }
 
 template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route>
 static hipError_t launch_rows_k(const S *a, S *b, const Geom &g, const Relax<T> &p, const StepLaunch &c,
                                 hipStream_t st) {
-    // inner rows, then the face rows
-    const RowLaunch L = row_launch(g, c.bx, c.by, c.xcd_remap);
-    const dim3 block(c.bx, c.by);
-    if (L.inner.rows > 0) {
-        hipLaunchKernelGGL((stream_collide_rows_kernel<S, T, Forced, LdAux, StAux, Route>), dim3(L.inner_blocks),
-                           block, 0, st, a, b, g, p, L.inner);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    const int threads = (c.bx * c.by + 63) / 64 * 64;
+    // near: the lattice, a layer and the descriptor's lead fit 32-bit offsets;
+    // far: the layers that a wave's nodes and their sources lie in do
+    const uint64_t row = (uint64_t)Q * sizeof(S) * (uint64_t)g.nx, layer = row * (uint64_t)g.ny;
+    const uint64_t bytes = layer * (uint64_t)g.nz;
+    const bool near = bytes + layer + 2 * row < 0xFFFFFF00ull;
+    const bool far = layer * (uint64_t)(64 / g.nxy + 5) + 2 * row < 0x80000000ull;
+    // Beyond 1 GiB FP32 and FP64 run 0-6% faster with offsets from the wave's
+    // own layer (300 x 280 x 290: 733 against 772 us FP32, 1220 against 1299
+    // FP64), FP16 between 3% faster and 4% slower.  From 4 GiB FP32 runs 2-6%
+    // faster with one wave per run of a row (512^3 3449 against 3524 us; 500^3,
+    // whole rows per workgroup, 3569 against 3784), FP64 and FP16 1-14% slower.
+    const bool prefer_far = !std::is_same<S, __half>::value && bytes > ((uint64_t)1 << 30);
+    const bool prefer_rows = std::is_same<S, float>::value && !near && g.nx >= 64;
+    if (!prefer_rows && (near || far)) {
+        FlatGrid L;
+        const uint32_t blocks = (uint32_t)(((int64_t)g.n + threads - 1) / threads);
+        L.by_nx = Divisor::make((uint32_t)g.nx);
+        L.by_ny = Divisor::make((uint32_t)g.ny);
+        L.aligned = blocks & ~7u;
+        L.remap = c.xcd_remap;
+        if (near && !(far && prefer_far))
+            hipLaunchKernelGGL((stream_collide_flat_kernel<S, T, Forced, LdAux, StAux, Route, false>), dim3(blocks),
+                               dim3(threads), 0, st, a, b, g, p, L);
+        else
+            hipLaunchKernelGGL((stream_collide_flat_kernel<S, T, Forced, LdAux, StAux, Route, true>), dim3(blocks),
+                               dim3(threads), 0, st, a, b, g, p, L);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL((stream_collide_rows_face_kernel<S, T, Forced, LdAux, StAux, Route>), dim3(L.face_blocks),
-                       block, 0, st, a, b, g, p, L.face);
+    RowGrid R;
+    const uint32_t blocks = all_rows(g, threads, c.xcd_remap, R);
+    hipLaunchKernelGGL((stream_collide_rows_kernel<S, T, Forced, LdAux, StAux, Route>), dim3(blocks), dim3(threads), 0,
+                       st, a, b, g, p, R);
     return hipGetLastError();
 }
 
@@ -116,18 +180,6 @@ static hipError_t launch_rows_f(const void *A, void *B, const Geom &g, const Rel
                                 hipStream_t st) {
     const S *a = (const S *)A;
     S *b = (S *)B;
-    if (c.bx % 64 != 0) {
-        LaunchGrid L;
-        L.gx = (g.nx + c.bx - 1) / c.bx;
-        L.gy = (g.ny + c.by - 1) / c.by;
-        L.gz = g.nz;
-        const uint32_t nb = L.gx * L.gy * L.gz;
-        L.aligned = nb & ~7u;
-        L.remap = c.xcd_remap;
-        hipLaunchKernelGGL((stream_collide_any_kernel<S, T, Forced, Route>), dim3(nb), dim3(c.bx, c.by), 0, st, a, b,
-                           g, p, L);
-        return hipGetLastError();
-    }
     if (Route != 0)     // the printed form and the comparison model: only the store hint is tunable
         return c.nt_stores ? launch_rows_k<S, T, Forced, 0, 2, Route>(a, b, g, p, c, st)
                            : launch_rows_k<S, T, Forced, 0, 0, Route>(a, b, g, p, c, st);

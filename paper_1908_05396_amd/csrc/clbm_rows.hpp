@@ -5,9 +5,7 @@
 // (19 r + a) nx + x (Geom::plane = nx, Geom::row = 19 nx).  A row kernel
 // runs waves of 64 consecutive x of one row (blockDim.x a multiple of 64),
 // so every direction's source or target run has a uniform (scalar) base and
-// one lane offset serves all of them.  Rows off the y and z faces and rows on
-// them go to separate launches: the inner-row kernels then carry no face
-// logic.
+// one lane offset serves all of them.
 #pragma once
 
 #include "clbm_internal.hpp"
@@ -18,23 +16,47 @@ __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const void *base, uint32_t byt
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, kBufferFlags);
 }
 
+// The work of a launch is a list of wave items, (row, run of 64 x) in x-fastest
+// order; workgroup b takes the items b W .. b W + W - 1 of its W waves, so a
+// lattice of any width fills whole workgroups and the runs of a row, which
+// share cache lines where they meet, stay together.
 struct RowGrid {
-    uint32_t gx;            // tiles along x
+    uint32_t gx;            // runs of 64 x per row
     uint32_t rows;          // rows handled by the launch
     uint32_t aligned;       // largest multiple of 8 <= number of workgroups
-    int32_t remap;          // XCD-contiguous tile order
+    int32_t remap;          // XCD-contiguous workgroup order
     int32_t zf, yf;         // face rows: z faces (1 or 2) and y faces (1 or 2)
 };
 
-// Row index of the wave and tile of the workgroup (blockDim.x a multiple of 64).
+// Column of the lane and row index of the wave.
 __device__ inline bool row_of(const RowGrid &R, int &x, uint32_t &ri) {
     uint32_t b = blockIdx.x;
     if (R.remap && b < R.aligned) b = (b & 7u) * (R.aligned >> 3) + (b >> 3);
-    const uint32_t tx = b % R.gx;
-    ri = __builtin_amdgcn_readfirstlane((b / R.gx) * blockDim.y + threadIdx.y);
-    x = (int)(tx * blockDim.x + threadIdx.x);
+    const uint32_t item = __builtin_amdgcn_readfirstlane(b * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    ri = item / R.gx;
+    x = (int)((item - ri * R.gx) * 64u + (threadIdx.x & 63u));
     return ri < R.rows;
 }
+
+// Quotient of a 32-bit value below 2^31 by a divisor fixed at launch, by one
+// high multiplication: with s = ceil(log2 d) and m = ceil(2^(31 + s) / d) <
+// 2^32, floor(m i / 2^(31 + s)) = floor(i / d) for i < 2^31 (the excess of m,
+// below d, adds less than i / 2^(31 + s) <= 1 / d to the quotient).
+struct Divisor {
+    uint32_t m, s;
+    static Divisor make(uint32_t d) {
+        uint32_t s = 0;
+        while ((1ull << s) < d) ++s;
+        return {(uint32_t)(((1ull << (31 + s)) + d - 1) / d), s};
+    }
+    __device__ uint32_t quotient(uint32_t i) const { return (uint32_t)(((uint64_t)m * i) >> 31 >> s); }
+};
+
+struct FlatGrid {
+    Divisor by_nx, by_ny;
+    uint32_t aligned;       // largest multiple of 8 <= number of workgroups
+    int32_t remap;          // XCD-contiguous workgroup order
+};
 
 // inner rows: y in [1, ny - 2], z in [1, nz - 2]
 __device__ inline void inner_row(const Geom &g, uint32_t ri, int &y, int &z) {
@@ -56,30 +78,30 @@ __device__ inline void face_row(const Geom &g, const RowGrid &R, uint32_t ri, in
     }
 }
 
-// Launch shapes of the inner-row and face-row kernels for blocks of bx x by
-// (bx a multiple of 64); inner rows may be none (ny or nz below 3).
-struct RowLaunch {
-    RowGrid inner, face;
-    uint32_t inner_blocks, face_blocks;
-};
-
-inline RowLaunch row_launch(const Geom &g, int bx, int by, int remap) {
-    RowLaunch L;
-    RowGrid R;
-    R.gx = (uint32_t)((g.nx + bx - 1) / bx);
+// Workgroups of `threads` threads (a multiple of 64) over `rows` rows.
+inline uint32_t row_blocks(const Geom &g, uint32_t rows, int threads, int remap, RowGrid &R) {
+    R.gx = ((uint32_t)g.nx + 63u) / 64u;
+    R.rows = rows;
     R.zf = g.nz > 1 ? 2 : 1;
     R.yf = g.ny > 1 ? 2 : 1;
     R.remap = remap;
-    R.rows = (g.ny > 2 && g.nz > 2) ? (uint32_t)(g.ny - 2) * (uint32_t)(g.nz - 2) : 0u;
-    L.inner_blocks = R.gx * ((R.rows + by - 1) / by);
-    R.aligned = L.inner_blocks & ~7u;
-    L.inner = R;
-    R.rows = (uint32_t)R.zf * (uint32_t)g.ny + (g.nz > 2 ? (uint32_t)(g.nz - 2) * (uint32_t)R.yf : 0u);
-    L.face_blocks = R.gx * ((R.rows + by - 1) / by);
-    R.aligned = L.face_blocks & ~7u;
-    R.remap = 0;
-    L.face = R;
-    return L;
+    const uint32_t waves = (uint32_t)threads / 64u;
+    const uint32_t blocks = (uint32_t)(((uint64_t)R.gx * rows + waves - 1) / waves);
+    R.aligned = blocks & ~7u;
+    return blocks;
+}
+
+// One launch over every row of the lattice, or the inner and the face rows
+// apart (the inner rows may be none: ny or nz below 3).
+inline uint32_t all_rows(const Geom &g, int threads, int remap, RowGrid &R) {
+    return row_blocks(g, (uint32_t)g.ny * (uint32_t)g.nz, threads, remap, R);
+}
+inline uint32_t inner_rows(const Geom &g, int threads, int remap, RowGrid &R) {
+    return row_blocks(g, (g.ny > 2 && g.nz > 2) ? (uint32_t)(g.ny - 2) * (uint32_t)(g.nz - 2) : 0u, threads, remap, R);
+}
+inline uint32_t face_rows(const Geom &g, int threads, RowGrid &R) {
+    const uint32_t zf = g.nz > 1 ? 2 : 1, yf = g.ny > 1 ? 2 : 1;
+    return row_blocks(g, zf * (uint32_t)g.ny + (g.nz > 2 ? (uint32_t)(g.nz - 2) * yf : 0u), threads, 0, R);
 }
 
 // Row kernels group the x-face bounce-back loads of a wave (row_gather's
@@ -101,121 +123,136 @@ struct Shift {
 };
 
 // Pull of node x of row (y, z) with the wall rules into d; y and z uniform
-// over the wave (or over each half, Pair); Face: the row lies on a y or z face;
-// XGroup: the x-face bounce-back loads of a wave issued together (below).
+// over the wave (or over each half, Pair); Face: the row may lie on a y or z
+// face; XGroup: the x-face bounce-back loads of a wave issued together (below).
+//
+// Nine source rows (one per e_y, e_z), each with a descriptor whose base lies
+// one value before the row group; direction a's run at the scalar offset
+// a nx.  The lane offset selects x - cx(a) + 1, wrapped on a periodic x axis;
+// it is shared by the directions of one cx.
 template <typename S, typename T, int LdAux, bool Face, bool Pair = false, bool XGroup = false>
 __device__ inline void row_gather(const S *__restrict__ A, const Geom &g, const Relax<T> &p, int x, int y, int z,
                                   T (&d)[Q], Shift sh = Shift{0u, 0u}) {
     static_assert(!(Pair && Face), "paired rows lie off the y and z faces");
     constexpr uint32_t es = sizeof(S);
-    const int64_t r = (int64_t)z * g.ny + y;
-    // Each direction reads a run of its source row through a base one value
-    // before the run; the lane offset selects x - cx(a) + 1, wrapped on a
-    // periodic x axis.  Offsets stay within nx + 2 values of the base.  On a
-    // non-periodic x face the source column x - cx(a) = -1 or nx is a ghost,
-    // whose value the x-face rule below supplies: those lanes take an offset
-    // beyond the descriptor's range, so the load returns 0 without touching
-    // memory (and the cache line past the run is not fetched for them).
-    // (the ranges pass through readfirstlane so that the compiler keeps the
-    // descriptors in scalar registers)
-    // (a second half's offsets, past D, stay outside too: D + (nx + 2) values < 2^31 bytes)
-    const uint32_t run_range = __builtin_amdgcn_readfirstlane((uint32_t)(g.nx + 2) * es);
-    const uint32_t range = Pair ? run_range + sh.range : run_range;
+    // On a non-periodic x face the source column x - cx(a) = -1 or nx is a
+    // ghost, whose value the x-face rule below supplies: those lanes take an
+    // offset beyond every descriptor's range, so the load returns 0 without
+    // touching memory (and the cache line past the run is not fetched for
+    // them).  (the lengths pass through readfirstlane so that the compiler
+    // keeps them in scalar registers; a second half's offsets, past D, and the
+    // run offsets stay below 2^31 bytes)
+    const uint32_t run = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
+    const uint32_t range = (uint32_t)(Q * run) + 2 * es + (Pair ? sh.range : 0u);
     const uint32_t add = Pair ? sh.lane : 0u;
     constexpr uint32_t outside = 0x80000000u;
     const uint32_t o0 = (uint32_t)(x + 1) * es + add;
-    const uint32_t op = (x == 0 ? (g.px ? run_range - 2 * es : outside) : (uint32_t)x * es) + add;     // cx = +1
+    const uint32_t op = (x == 0 ? (g.px ? run : outside) : (uint32_t)x * es) + add;                  // cx = +1
     const uint32_t om = (x == g.nx - 1 ? (g.px ? es : outside) : (uint32_t)(x + 2) * es) + add;      // cx = -1
     auto lane_off = [&](int a) { return cx(a) == 1 ? op : (cx(a) == -1 ? om : o0); };
-    auto run = [&](int a, int64_t row) {
-        return row_rsrc(A + row * g.row + (int64_t)a * g.nx - 1, range);
-    };
-    // the node's own row group, for the bounce-back values (slot in the lane offset)
-    const uint32_t own_range = __builtin_amdgcn_readfirstlane((uint32_t)Q * (uint32_t)g.nx * es);
-    const __amdgpu_buffer_rsrc_t own_rsrc = row_rsrc(A + r * g.row, Pair ? own_range + sh.range : own_range);
-    auto own = [&](int a) {
-        return (T)RawBits<S>::template load<LdAux>(own_rsrc, (uint32_t)(opp(a) * g.nx + x) * es + add);
-    };
+    const int64_t row = g.row, layer = (int64_t)g.ny * g.row;
+    const S *own = A + ((int64_t)z * layer + (int64_t)y * row) - 1;
+    // source ghosts beyond the y and z walls (index c + 1 for c = -1, 0, +1)
+    const int ylo = y == 0, yhi = y == g.ny - 1, zlo = z == 0, zhi = z == g.nz - 1;
+    const int gy[3] = {yhi & (g.py ^ 1), 0, ylo & (g.py ^ 1)};
+    const int gz[3] = {zhi & (g.pz ^ 1), 0, zlo & (g.pz ^ 1)};
+    auto row_wall = [&](int a) { return Face && ((gy[cy(a) + 1] | gz[cz(a) + 1]) != 0); };
     if constexpr (!Face) {
 #pragma unroll
         for (int a = 0; a < Q; ++a)
-            d[a] = (T)RawBits<S>::template load<LdAux>(run(a, r - cy(a) - (int64_t)cz(a) * g.ny), lane_off(a));
+            d[a] = (T)RawBits<S>::template load<LdAux>(row_rsrc(own - cy(a) * row - cz(a) * layer, range), lane_off(a),
+                                                       (uint32_t)a * run);
     } else {
-        // rows on a y or z face: per direction (uniformly) the source row is
-        // inside, wrapped on a periodic axis, or a ghost: half-way bounce-back
-        // returns the node's own population opposite to a, plus the
-        // moving-wall term for a ghost in the lid plane
-        const int m = g.lid_mask;
+        // per direction (uniformly) the source row is inside, wrapped on a
+        // periodic axis, or a ghost: half-way bounce-back returns the node's
+        // own population opposite to a, plus the moving-wall term for a ghost
+        // in the lid plane.  Which run is read is a scalar select, so the 19
+        // loads go out together and the wave waits for memory once; the lid
+        // terms are added afterwards.
+        const int64_t dy[3] = {yhi ? row - layer : row, 0, ylo ? layer - row : -row};
+        const int64_t lattice = (int64_t)g.nz * layer;
+        const int64_t dz[3] = {zhi ? layer - lattice : layer, 0, zlo ? lattice - layer : -layer};
 #pragma unroll
         for (int a = 0; a < Q; ++a) {
-            int sy = y - cy(a), sz = z - cz(a);
-            bool wall = false;
-            if (sy < 0 || sy >= g.ny) { if (g.py) sy = sy < 0 ? sy + g.ny : sy - g.ny; else wall = true; }
-            if (sz < 0 || sz >= g.nz) { if (g.pz) sz = sz < 0 ? sz + g.nz : sz - g.nz; else wall = true; }
-            if (!wall) {
-                d[a] = (T)RawBits<S>::template load<LdAux>(run(a, (int64_t)sz * g.ny + sy), lane_off(a));
-            } else {
-                const int sx = x - cx(a);
-                const bool in_lid = ((m & 4) && sy == -1) || ((m & 8) && sy == g.ny) || ((m & 16) && sz == -1) ||
-                                    ((m & 32) && sz == g.nz) || ((m & 1) && sx == -1) || ((m & 2) && sx == g.nx);
-                d[a] = wall_value<T>(own(a), p, a, in_lid);
+            const bool wall = row_wall(a);
+            const S *src = own + (wall ? 0 : dy[cy(a) + 1] + dz[cz(a) + 1]);
+            const uint32_t o = cx(a) == 0 ? o0 : (wall ? o0 : lane_off(a));
+            d[a] = (T)RawBits<S>::template load<LdAux>(row_rsrc(src, range), o, (uint32_t)(wall ? opp(a) : a) * run);
+            // (each direction's scalars end with its load: all of them together
+            // would not fit the scalar registers)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the lid is one face, so a ghost lies in its plane through one axis
+        const int m = g.lid_mask;
+        auto lid_y = [&](int c) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a)
+                if (cy(a) == c) d[a] = wall_value<T>(d[a], p, a, true);
+        };
+        auto lid_z = [&](int c) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a)
+                if (cz(a) == c) d[a] = wall_value<T>(d[a], p, a, true);
+        };
+        if ((m & 4) && ylo) lid_y(1);
+        if ((m & 8) && yhi) lid_y(-1);
+        if ((m & 16) && zlo) lid_z(1);
+        if ((m & 32) && zhi) lid_z(-1);
+        if (m & 3) {
+            // lid on an x face: its lanes' ghosts beyond a y or z wall lie in its plane too
+#pragma unroll
+            for (int a = 1; a < Q; ++a) {
+                if (cx(a) == 0) continue;
+                const bool in_lid = row_wall(a) && (cx(a) == 1 ? (m & 1) && x == 0 : (m & 2) && x == g.nx - 1);
+                d[a] = wall_value<T>(d[a], p, a, in_lid);
             }
         }
     }
     // lanes on a non-periodic x face: directions whose source row is inside
     // the lattice but whose source column is a ghost take the bounce-back of
-    // the node's own opposite population (XGroup: the wave issues these loads
-    // all together, the lanes without such a ghost taking an out-of-range
-    // offset, i.e. no memory access, and selects the wall values afterwards,
-    // so that it waits for memory once instead of once per direction)
+    // the node's own opposite population (those whose source row is a ghost
+    // have bounced back above, with the lid term of every ghost coordinate).
+    // XGroup: the wave issues these loads all together, the lanes without such
+    // a ghost taking an out-of-range offset, i.e. no memory access, and selects
+    // the wall values afterwards, so that it waits for memory once instead of
+    // once per direction.
+    if (g.px) return;
+    const bool lo = x == 0, hi = x == g.nx - 1;
+    const __amdgpu_buffer_rsrc_t own_rsrc = row_rsrc(own, range);
+    auto bounce = [&](int a, uint32_t o) {
+        return (T)RawBits<S>::template load<LdAux>(own_rsrc, o, (uint32_t)opp(a) * run);
+    };
     if constexpr (!XGroup) {
-        if (!g.px && (x == 0 || x == g.nx - 1)) {
+        if (lo || hi) {
 #pragma unroll
             for (int a = 1; a < Q; ++a) {
-                if (cx(a) == 0 || !((x == 0 && cx(a) == 1) || (x == g.nx - 1 && cx(a) == -1))) continue;
-                const int sy = y - cy(a), sz = z - cz(a);
-                const bool row_wall = (!g.py && (sy < 0 || sy >= g.ny)) || (!g.pz && (sz < 0 || sz >= g.nz));
-                if (row_wall) continue;     // bounced back above, with the lid term of every ghost coordinate
-                d[a] = wall_value<T>(own(a), p, a, (g.lid_mask & (cx(a) == 1 ? 1 : 2)) != 0);
+                if (cx(a) == 0 || !(cx(a) == 1 ? lo : hi) || row_wall(a)) continue;
+                d[a] = wall_value<T>(bounce(a, o0), p, a, (g.lid_mask & (cx(a) == 1 ? 1 : 2)) != 0);
             }
         }
-    } else if (!g.px) {
-        const bool lo = x == 0, hi = x == g.nx - 1;
-        if (__builtin_amdgcn_ballot_w64(lo || hi) != 0) {       // uniform over the wave
-            T o[Q];
+    } else if (__builtin_amdgcn_ballot_w64(lo || hi) != 0) {       // uniform over the wave
+        const uint32_t ol = lo ? o0 : outside, oh = hi ? o0 : outside;
+        T o[Q];
 #pragma unroll
-            for (int a = 1; a < Q; ++a) {
-                if (cx(a) == 0) continue;
-                const bool ghost = cx(a) == 1 ? lo : hi;
-                o[a] = (T)RawBits<S>::template load<LdAux>(
-                    own_rsrc, ghost ? (uint32_t)(opp(a) * g.nx + x) * es + add : outside);
-            }
+        for (int a = 1; a < Q; ++a)
+            if (cx(a) != 0) o[a] = bounce(a, cx(a) == 1 ? ol : oh);
 #pragma unroll
-            for (int a = 1; a < Q; ++a) {
-                if (cx(a) == 0) continue;
-                const int sy = y - cy(a), sz = z - cz(a);
-                const bool row_wall = (!g.py && (sy < 0 || sy >= g.ny)) || (!g.pz && (sz < 0 || sz >= g.nz));
-                if (row_wall) continue;     // bounced back above, with the lid term of every ghost coordinate
-                const bool ghost = cx(a) == 1 ? lo : hi;
-                const T w = wall_value<T>(o[a], p, a, (g.lid_mask & (cx(a) == 1 ? 1 : 2)) != 0);
-                d[a] = ghost ? w : d[a];
-            }
+        for (int a = 1; a < Q; ++a) {
+            if (cx(a) == 0) continue;
+            const bool ghost = (cx(a) == 1 ? lo : hi) && !row_wall(a);
+            const T w = wall_value<T>(o[a], p, a, (g.lid_mask & (cx(a) == 1 ? 1 : 2)) != 0);
+            d[a] = ghost ? w : d[a];
         }
     }
 }
 
-// Store of the 19 populations of node x of row (y, z) (y, z uniform; Pair:
-// the second half's lanes shifted as in row_gather).  FP16 with stochastic
-// rounding (sr): rounded in the store itself with the seeds of round_state
-// (sr_base = sr_base(node, step)).
-template <typename S, typename T, int StAux, bool Pair = false>
-__device__ inline void row_store(S *__restrict__ B, const Geom &g, int x, int y, int z, const T (&d)[Q],
-                                 bool sr = false, uint32_t seed_base = 0, Shift sh = Shift{0u, 0u}) {
-    constexpr uint32_t es = sizeof(S);
-    const uint32_t run_range = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
-    const uint32_t srange = Pair ? run_range + sh.range : run_range;
-    S *out = B + ((int64_t)z * g.ny + y) * g.row;
-    const uint32_t lane = (uint32_t)x * es + (Pair ? sh.lane : 0u);
+// Store of the 19 populations at lane byte offset `lane` of `out`, the run of
+// direction a at the scalar offset a * run.  FP16 with stochastic rounding (sr):
+// rounded in the store itself with the seeds of round_state (sr_base =
+// sr_base(node, step)).
+template <typename S, typename T, int StAux>
+__device__ inline void row_store_at(__amdgpu_buffer_rsrc_t out, uint32_t lane, uint32_t run, const T (&d)[Q], bool sr,
+                                    uint32_t seed_base) {
     if constexpr (std::is_same<S, __half>::value) {
         if (sr) {
             // each conversion keeps the high half of its first operand: the
@@ -227,15 +264,26 @@ __device__ inline void row_store(S *__restrict__ B, const Geom &g, int x, int y,
 #pragma unroll
             for (int a = 0; a < Q; ++a) {
                 h = __builtin_amdgcn_cvt_sr_f16_f32(h, (float)d[a], seed_base + (uint32_t)a * kWeyl, false);
-                __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, h[0]),
-                                                      row_rsrc(out + (int64_t)a * g.nx, srange), (int)lane, 0, StAux);
+                __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, h[0]), out, (int)lane,
+                                                      (int)((uint32_t)a * run), StAux);
             }
             return;
         }
     }
 #pragma unroll
-    for (int a = 0; a < Q; ++a)
-        RawBits<S>::template store<StAux>(row_rsrc(out + (int64_t)a * g.nx, srange), lane, d[a]);
+    for (int a = 0; a < Q; ++a) RawBits<S>::template store<StAux>(out, lane, d[a], (uint32_t)a * run);
+}
+
+// Store at node x of row (y, z) (y, z uniform; Pair: the second half's lanes
+// shifted as in row_gather).
+template <typename S, typename T, int StAux, bool Pair = false>
+__device__ inline void row_store(S *__restrict__ B, const Geom &g, int x, int y, int z, const T (&d)[Q],
+                                 bool sr = false, uint32_t seed_base = 0, Shift sh = Shift{0u, 0u}) {
+    constexpr uint32_t es = sizeof(S);
+    const uint32_t run = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
+    const __amdgpu_buffer_rsrc_t out =
+        row_rsrc(B + ((int64_t)z * g.ny + y) * g.row, (uint32_t)Q * run + (Pair ? sh.range : 0u));
+    row_store_at<S, T, StAux>(out, (uint32_t)x * es + (Pair ? sh.lane : 0u), run, d, sr, seed_base);
 }
 
 // One step of node x of row (y, z): gather, collide, store; `step` is the
