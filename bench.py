@@ -248,7 +248,7 @@ def batched(clbm, torch, W, storage, steps, spinup, tune=True):
         ms[key] = e0.elapsed_time(e1) / steps
         out[key] = round(nodes * steps / (time.perf_counter() - t0) / 1e6, 1)
     out["speedup"] = round(out["mlups"] / out["mlups_one_launch_per_instance"], 3)
-    kernel = "batch_packed" if cfg.get("passes", 0) > 0 else "batch_rows"
+    kernel = "batch_rows"
     out["roofline"] = roofline(storage, nodes, ms["mlups"], BATCH_WORKLOAD, 1, "rows", kernel=kernel)
     r = b.reduce(raise_unstable=False)
     out["nonfinite_instances"] = sum(1 for x in r if x["nonfinite"] > 0)

@@ -345,10 +345,8 @@ const char *clbm_last_error(void);
  * hipGraph and replayed.  All instances share the storage type and the
  * layout (EINVAL otherwise).  Instance i occupies clbm_buffer_size bytes of
  * its params, rounded up to 256, at a 256-byte-aligned offset of each pool, in
- * instance order.  Row layout: each wave takes (instance, z layer, k passes
- * of 64 consecutive nodes) items, or (instance, row, run of 64 x) items, the
- * short tails (at most 32 values) of two inner rows of an instance sharing
- * one wave, a 32-lane half each; planes: each workgroup takes (instance,
+ * instance order.  Row layout: each wave takes (instance, 64 consecutive nodes)
+ * items, or k such groups; planes: each workgroup takes (instance,
  * z layer, run of bx nodes) tiles.
  * Row-layout instances hold less than 2 GiB of state each.
  * ------------------------------------------------------------------------ */
@@ -356,7 +354,7 @@ typedef struct clbm_batch clbm_batch;
 
 typedef struct {
     int32_t bx, by;            /* threads per workgroup, a multiple of 64, <= 512 (<= 256 for FP64;
-                                  default: that maximum);
+                                  default: that maximum, 256 in the row layout with FP32 storage);
                                   planes: the tile is bx consecutive nodes of one z layer (x fastest);
                                   rows: bx / 64 waves, each on its own items; by must be 1 */
     int32_t blocks_per_cu;     /* grid = blocks_per_cu x CUs workgroups (1..1024), at most one item
@@ -367,11 +365,8 @@ typedef struct {
     int32_t nt_stores;         /* 1: non-temporal (streaming) stores, 0: plain stores (default: the
                                   short runs of small lattices leave partial cache lines, which plain
                                   stores let the cache merge) */
-    int32_t passes;            /* row layout: 0 = each wave item is one row's run of 64 x, or the short
-                                  tails of two inner rows (default);
-                                  k > 0 = each item is k passes of 64 consecutive nodes of a z layer
-                                  (rows packed into whole waves: fewer idle lanes for narrow lattices,
-                                  per-lane row addressing); planes layout: must be 0 */
+    int32_t passes;            /* row layout: k > 1 = each wave item is k groups of 64 consecutive
+                                  nodes, else one group (default 0); planes layout: must be 0 */
 } clbm_batch_config;
 
 /* Bytes each of the two pools must hold for these instances. */

@@ -10,10 +10,8 @@
 // workgroup b processes tiles b, b + G, b + 2G, ... of a flattened tile list,
 // each tile being (instance, z layer, run of bx consecutive nodes of that
 // layer in x-fastest order), so small lattices leave no lanes idle except at
-// the end of a layer.  Row layout: every wave takes items (instance, row, run
-// of 64 x) of a flattened list in the same strided way, so the wave's row is
-// uniform and its populations come through scalar row bases, with the face
-// rules taken per wave (rows on a y or z face) or per lane (x faces).  k
+// the end of a layer.  Row layout: every wave takes items (instance, 64
+// consecutive nodes) of a flattened list in the same strided way.  k
 // consecutive steps are captured into a hipGraph on a library stream and
 // replayed on the caller's stream.
 #include <algorithm>
@@ -29,18 +27,10 @@ template <typename T> struct BatchInst {
     Relax<T> p;
     int64_t base;       // element offset of the instance's state in each pool
     uint32_t tile0;     // first tile of the instance in the flattened list
-    uint32_t chunks;    // tiles per z layer (planes), 64-wide runs per row (rows), or packed items per z
-                        // layer (rows, packed)
-    float inv_nx;       // 1 / nx, for the row of a node within a layer
+    uint32_t chunks;    // tiles per z layer (planes)
+    float inv_nx;       // 1 / nx, for the row of a node within a layer (planes)
+    Divisor by_nx, by_ny;   // rows: row and layer of a node
     int32_t forced;
-    uint32_t bytes;     // bytes of the instance's state (row layout, packed items)
-};
-
-// Row-layout work item of one wave: the 64-wide run from x0 of row `row`
-// (pair = 0), or the short tails from x0 of two inner rows `row` and
-// row + pair, one per half of the wave (tails of at most 32 values).
-struct alignas(16) RowItem {
-    int32_t inst, row, x0, pair;
 };
 
 // The collision index of a launch (it keys the stochastic rounding of FP16
@@ -81,54 +71,63 @@ batch_step_kernel(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T>
     }
 }
 
-template <typename S, typename T, bool Forced, int Route, int StAux>
-__device__ inline void batch_row(const S *A, S *B, const Geom &g, const Relax<T> &p, int x, int y, int z,
-                                 uint32_t step) {
-    if (y == 0 || y == g.ny - 1 || z == 0 || z == g.nz - 1)
-        row_step<S, T, Forced, 0, StAux, Route, true, XGroupRows<S>::value>(A, B, g, p, x, y, z, step);
+// Row layout: a wave takes items of 64 consecutive nodes of an instance (x
+// fastest, across rows and layers; `groups` of them per item), gathered with
+// the full wall rule by address selects as in the single-lattice flat kernel:
+// no idle lanes but in an instance's last item, and no separate faces.
+//
+// Bound: HBM and issue.  64 cavities of edge 32 to 96, FP32: 617 us per
+// step, 5.3 TB/s (682 with an item per run of a row, the short tails of two
+// rows sharing a wave: 1.19 lanes per node and a second round of loads for the
+// x faces).
+template <typename S, typename T, int Route, int StAux, bool AnyForced>
+__device__ __forceinline__ void batch_nodes(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T> &in, uint32_t n,
+                                   uint32_t step) {
+    const Geom g = in.g;
+    if (n >= (uint32_t)g.n) return;
+    const Relax<T> p = in.p;        // a copy: read once per item, not at each use
+    const S *Ai = A + in.base;
+    S *Bi = B + in.base;
+    const uint32_t r = in.by_nx.quotient(n), zr = in.by_ny.quotient(r);
+    const int x = (int)(n - r * (uint32_t)g.nx), y = (int)(r - zr * (uint32_t)g.ny), z = (int)zr;
+    const uint32_t run = (uint32_t)g.nx * (uint32_t)sizeof(S);
+    const uint32_t own = r * (Q * run) + (uint32_t)x * (uint32_t)sizeof(S);
+    T d[Q];
+    gather_flat<S, T, 0, false>(Ai, own, g, p, x, y, z, d);
+    if (AnyForced && in.forced)
+        collide<T, true, Route, NewtonSteps<S>::value>(d, p, nullptr);
     else
-        row_step<S, T, Forced, 0, StAux, Route, false, XGroupRows<S>::value>(A, B, g, p, x, y, z, step);
+        collide<T, false, Route, NewtonSteps<S>::value>(d, p, nullptr);
+    row_store_at<S, T, StAux>(row_rsrc(Bi, 0xFFFFFFFFu), own, run, d, p.sr != 0, sr_base(n, step));
 }
 
-template <typename S, typename T, int Route, int StAux, bool AnyForced>
+// Loop: a wave strides over items, or an item holds several groups of nodes.
+// Without it (one item of 64 nodes per wave, the default) the compiler keeps
+// no loop-invariant constants alive: 62 instead of 86 VGPRs in FP32.
+template <typename S, typename T, int Route, int StAux, bool AnyForced, bool Loop>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
 batch_rows_kernel(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T> *__restrict__ inst,
-                  const RowItem *__restrict__ items, uint32_t nitems, const uint32_t *__restrict__ step_base,
-                  uint32_t step_off) {
+                  const int32_t *__restrict__ tile_inst, uint32_t ntiles, uint32_t groups,
+                  const uint32_t *__restrict__ step_base, uint32_t step_off) {
     const uint32_t step = __builtin_amdgcn_readfirstlane(*step_base + step_off);
     const uint32_t waves = blockDim.x >> 6;
     // XCD-contiguous order: workgroups wg, wg + 8, ... run on one XCD, so they
     // take consecutive items, and the partial cache lines that neighbouring
-    // rows share meet in that XCD's L2
+    // items share meet in that XCD's L2
     uint32_t wg = blockIdx.x;
     const uint32_t aligned = gridDim.x & ~7u;
     if (wg < aligned) wg = (wg & 7u) * (aligned >> 3) + (wg >> 3);
-    const uint32_t w0 = wg * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = (int)(threadIdx.x & 63u);
-    for (uint32_t t = w0; t < nitems; t += gridDim.x * waves) {
-        const int i = __builtin_amdgcn_readfirstlane(items[t].inst);
-        const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane(items[t].row);
-        const int x0 = __builtin_amdgcn_readfirstlane(items[t].x0);
-        const uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane(items[t].pair);
-        const Geom g = inst[i].g;
-        const int64_t base = inst[i].base;
-        const int y = (int)(row % (uint32_t)g.ny), z = (int)(row / (uint32_t)g.ny);
-        const Relax<T> p = inst[i].p;       // a copy: read once per item, not at each use
-        const bool forced = AnyForced && inst[i].forced;
-        if (k == 0) {
-            const int x = x0 + lane;
-            if (x >= g.nx) continue;
-            if (forced)
-                batch_row<S, T, true, Route, StAux>(A + base, B + base, g, p, x, y, z, step);
-            else
-                batch_row<S, T, false, Route, StAux>(A + base, B + base, g, p, x, y, z, step);
-        } else {
-            const int x = x0 + (lane & 31);
-            if (x >= g.nx) continue;
-            if (forced)
-                row_step_pair<S, T, true, 0, StAux, Route>(A + base, B + base, g, p, x, y, z, k, lane >= 32, step);
-            else
-                row_step_pair<S, T, false, 0, StAux, Route>(A + base, B + base, g, p, x, y, z, k, lane >= 32, step);
+    uint32_t t = __builtin_amdgcn_readfirstlane(wg * waves + (threadIdx.x >> 6));
+    const uint32_t lane = threadIdx.x & 63u;
+    if constexpr (!Loop) {
+        if (t >= ntiles) return;
+        const BatchInst<T> &in = inst[__builtin_amdgcn_readfirstlane(tile_inst[t])];
+        batch_nodes<S, T, Route, StAux, AnyForced>(A, B, in, (t - in.tile0) * 64u + lane, step);
+    } else {
+        for (; t < ntiles; t += gridDim.x * waves) {
+            const BatchInst<T> &in = inst[__builtin_amdgcn_readfirstlane(tile_inst[t])];
+            for (uint32_t j = 0; j < groups; ++j)
+                batch_nodes<S, T, Route, StAux, AnyForced>(A, B, in, ((t - in.tile0) * groups + j) * 64u + lane, step);
         }
     }
 }
@@ -138,117 +137,6 @@ struct BatchStep {
     uint32_t off;           // this launch's place in the run (1, 2, ...)
 };
 
-// ---------------------------------------------------------------------------
-// Packed items (row layout): a wave takes `passes` passes of 64 consecutive
-// nodes of one z layer, so a pass may hold the ends and starts of several
-// rows and a lattice of any width fills whole waves.  Each lane addresses its
-// own row through one buffer descriptor per instance (byte offset of element
-// (19 r + a) nx + x); the offset of direction a's source is the lane's offset
-// plus a uniform constant.  A pass whose lanes all lie off the y and z faces
-// takes that uniform pull, with the x-face lanes redone; a pass touching a
-// face row takes the full wall rule per lane.  Consecutive passes of a layer
-// stay in one wave, so the cache lines two neighbouring rows share are read
-// and written by the same wave.
-// ---------------------------------------------------------------------------
-template <typename S, typename T, bool Forced, int Route, int StAux>
-__device__ inline void packed_pass(const S *__restrict__ A, S *__restrict__ B, const Geom &g, const Relax<T> &p,
-                                   uint32_t bytes, float inv_nx, uint32_t l, int z, uint32_t step) {
-    constexpr int es = (int)sizeof(S);
-    const bool active = l < (uint32_t)g.nxy;
-    // row y = l / nx: float estimate, corrected to the exact quotient (l < 2^22)
-    int y = (int)((float)l * inv_nx);
-    if ((uint32_t)y * (uint32_t)g.nx > l) --y;
-    if ((uint32_t)(y + 1) * (uint32_t)g.nx <= l) ++y;
-    const int x = (int)(l - (uint32_t)y * (uint32_t)g.nx);
-    const bool face = y == 0 || y >= g.ny - 1 || z == 0 || z == g.nz - 1;
-    const bool any_face = __any(active && face);
-    if (!active) return;
-    const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, __builtin_amdgcn_readfirstlane(bytes));
-    const __amdgpu_buffer_rsrc_t rb = row_rsrc(B, __builtin_amdgcn_readfirstlane(bytes));
-    const int nx = g.nx, ny = g.ny;
-    const int lane_el = (Q * (y + ny * z)) * nx + x;             // element of (a = 0, x) in the row group
-    auto own = [&](int a) { return (T)RawBits<S>::template load<0>(ra, (uint32_t)((lane_el + opp(a) * nx) * es)); };
-    T d[Q];
-    if (!any_face) {
-#pragma unroll
-        for (int a = 0; a < Q; ++a) {
-            const int c = (a - Q * cy(a) - Q * cz(a) * ny) * nx - cx(a);
-            d[a] = (T)RawBits<S>::template load<0>(ra, (uint32_t)((lane_el + c) * es));
-        }
-        if (x == 0 || x == nx - 1) {
-#pragma unroll
-            for (int a = 1; a < Q; ++a) {
-                if (!((x == 0 && cx(a) == 1) || (x == nx - 1 && cx(a) == -1))) continue;
-                if (g.px) {
-                    const int c = (a - Q * cy(a) - Q * cz(a) * ny) * nx - cx(a) + (cx(a) == 1 ? nx : -nx);
-                    d[a] = (T)RawBits<S>::template load<0>(ra, (uint32_t)((lane_el + c) * es));
-                } else {
-                    d[a] = wall_value<T>(own(a), p, a, (g.lid_mask & (cx(a) == 1 ? 1 : 2)) != 0);
-                }
-            }
-        }
-    } else {
-        d[0] = (T)RawBits<S>::template load<0>(ra, (uint32_t)(lane_el * es));
-#pragma unroll
-        for (int a = 1; a < Q; ++a) {
-            int sx = x - cx(a), sy = y - cy(a), sz = z - cz(a);
-            const bool in_lid = ghost_in_lid(g, sx, sy, sz);
-            bool wall = false;
-            if (sx < 0 || sx >= nx) { if (g.px) sx = sx < 0 ? sx + nx : sx - nx; else wall = true; }
-            if (sy < 0 || sy >= ny) { if (g.py) sy = sy < 0 ? sy + ny : sy - ny; else wall = true; }
-            if (sz < 0 || sz >= g.nz) { if (g.pz) sz = sz < 0 ? sz + g.nz : sz - g.nz; else wall = true; }
-            if (!wall)
-                d[a] = (T)RawBits<S>::template load<0>(ra, (uint32_t)(((Q * (sy + ny * sz) + a) * nx + sx) * es));
-            else
-                d[a] = wall_value<T>(own(a), p, a, in_lid);
-        }
-    }
-    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    if constexpr (std::is_same<S, __half>::value) {
-        if (p.sr) {
-            const uint32_t base = sr_base(l + (uint32_t)g.nxy * (uint32_t)z, step);
-#pragma unroll
-            for (int a = 0; a < Q; ++a)
-                RawBits<S>::template store_sr<StAux>(rb, (uint32_t)((lane_el + a * nx) * es), d[a],
-                                                     base + (uint32_t)a * kWeyl);
-            return;
-        }
-    }
-#pragma unroll
-    for (int a = 0; a < Q; ++a) RawBits<S>::template store<StAux>(rb, (uint32_t)((lane_el + a * nx) * es), d[a]);
-}
-
-template <typename S, typename T, int Route, int StAux, bool AnyForced>
-__global__ void __launch_bounds__(MaxThreads<T>::value)
-batch_packed_kernel(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T> *__restrict__ inst,
-                    const int32_t *__restrict__ tile_inst, uint32_t ntiles, uint32_t passes,
-                    const uint32_t *__restrict__ step_base, uint32_t step_off) {
-    const uint32_t step = __builtin_amdgcn_readfirstlane(*step_base + step_off);
-    const uint32_t waves = blockDim.x >> 6;
-    const uint32_t w0 = blockIdx.x * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t lane = threadIdx.x & 63u;
-    for (uint32_t t = w0; t < ntiles; t += gridDim.x * waves) {
-        const int i = __builtin_amdgcn_readfirstlane(tile_inst[t]);
-        const Geom g = inst[i].g;
-        const int64_t base = inst[i].base;
-        const uint32_t local = t - inst[i].tile0;
-        const uint32_t chunks = inst[i].chunks;
-        const int z = (int)(local / chunks);
-        const uint32_t l0 = (local - (uint32_t)z * chunks) * passes * 64u;
-        const Relax<T> p = inst[i].p;       // a copy: read once per item, not at each use
-        const uint32_t bytes = inst[i].bytes;
-        const float inv_nx = inst[i].inv_nx;
-        for (uint32_t j = 0; j < passes; ++j) {
-            const uint32_t l = l0 + j * 64u;
-            if (l >= (uint32_t)g.nxy) break;
-            if (AnyForced && inst[i].forced)
-                packed_pass<S, T, true, Route, StAux>(A + base, B + base, g, p, bytes, inv_nx, l + lane, z, step);
-            else
-                packed_pass<S, T, false, Route, StAux>(A + base, B + base, g, p, bytes, inv_nx, l + lane, z, step);
-        }
-    }
-}
-
 template <typename S, typename T, int StAux, bool AF>
 static hipError_t launch_batch_h(const void *A, void *B, const void *inst, const int32_t *tiles, uint32_t ntiles,
                                  int route, bool rows, uint32_t passes, dim3 grid, dim3 block, BatchStep s,
@@ -256,22 +144,12 @@ static hipError_t launch_batch_h(const void *A, void *B, const void *inst, const
     const S *a = (const S *)A;
     S *b = (S *)B;
     const BatchInst<T> *d = (const BatchInst<T> *)inst;
-    if (rows && passes > 0) {
-        if (route == 0)
-            hipLaunchKernelGGL((batch_packed_kernel<S, T, 0, StAux, AF>), grid, block, 0, st, a, b, d, tiles, ntiles,
-                               passes, s.base, s.off);
-        else
-            hipLaunchKernelGGL((batch_packed_kernel<S, T, 1, StAux, AF>), grid, block, 0, st, a, b, d, tiles, ntiles,
-                               passes, s.base, s.off);
-        return hipGetLastError();
-    }
     if (rows) {
-        if (route == 0)
-            hipLaunchKernelGGL((batch_rows_kernel<S, T, 0, StAux, AF>), grid, block, 0, st, a, b, d,
-                               (const RowItem *)tiles, ntiles, s.base, s.off);
-        else
-            hipLaunchKernelGGL((batch_rows_kernel<S, T, 1, StAux, AF>), grid, block, 0, st, a, b, d,
-                               (const RowItem *)tiles, ntiles, s.base, s.off);
+        const uint32_t groups = passes > 0 ? passes : 1u;
+        const bool loop = groups > 1 || (uint64_t)grid.x * (block.x / 64u) < ntiles;
+        auto k = route == 0 ? (loop ? batch_rows_kernel<S, T, 0, StAux, AF, true> : batch_rows_kernel<S, T, 0, StAux, AF, false>)
+                            : (loop ? batch_rows_kernel<S, T, 1, StAux, AF, true> : batch_rows_kernel<S, T, 1, StAux, AF, false>);
+        hipLaunchKernelGGL(k, grid, block, 0, st, a, b, d, tiles, ntiles, groups, s.base, s.off);
         return hipGetLastError();
     }
     if (route == 0)
@@ -346,8 +224,8 @@ struct clbm_batch {
     // device tables
     uint32_t *d_step;       // collision index before the current run of launches
     void *d_inst;
-    int32_t *d_tiles;       // tile list: instance per tile, or RowItem (4 values) per row item
-    size_t tile_cap;        // int32 values
+    int32_t *d_tiles;       // tile list: instance per tile
+    size_t tile_cap;
     uint32_t ntiles;
     // reductions
     double *partials;
@@ -409,62 +287,20 @@ clbm_status upload_tables_t(clbm_batch *b, const std::vector<Relax<T>> &relax) {
         d.inv_nx = 1.0f / (float)g.nx;
         d.tile0 = (uint32_t)total;
         d.forced = b->forced[i];
-        d.bytes = (uint32_t)state_bytes_of(&b->prm[i]);
-        if (b->rows && b->cfg.passes > 0) {
-            const uint64_t per = 64ull * (uint64_t)b->cfg.passes;
-            d.chunks = (uint32_t)(((uint64_t)g.nxy + per - 1) / per);
-            total += (uint64_t)d.chunks * (uint64_t)g.nz;
-        } else if (b->rows) {
-            d.chunks = (uint32_t)((g.nx + 63) / 64);
+        d.by_nx = Divisor::make((uint32_t)g.nx);
+        d.by_ny = Divisor::make((uint32_t)g.ny);
+        if (b->rows) {
+            const uint64_t per = 64ull * (uint64_t)std::max(b->cfg.passes, 1);
+            total += ((uint64_t)g.n + per - 1) / per;
         } else {
             d.chunks = (uint32_t)((g.nxy + b->cfg.bx - 1) / b->cfg.bx);
             total += (uint64_t)d.chunks * (uint64_t)g.nz;
         }
     }
-    const bool per_row = b->rows && b->cfg.passes == 0;
-    if (per_row) {
-        // row items in row order; the short tails (at most 32 values) of two
-        // consecutive inner rows share a wave, one per half
-        for (int i = 0; i < b->count; ++i) {
-            const Geom &g = b->geom[i];
-            const int32_t chunks = (int32_t)inst[i].chunks, tail = g.nx % 64;
-            const bool short_tail = tail != 0 && tail <= 32;
-            const int32_t x_tail = 64 * (chunks - 1);
-            int32_t pending = -1;
-            inst[i].tile0 = (uint32_t)(tiles.size() / 4);
-            auto push = [&](int32_t row, int32_t x0, int32_t pair) {
-                tiles.push_back(i);
-                tiles.push_back(row);
-                tiles.push_back(x0);
-                tiles.push_back(pair);
-            };
-            for (int32_t z = 0; z < g.nz; ++z)
-                for (int32_t y = 0; y < g.ny; ++y) {
-                    const int32_t row = y + g.ny * z;
-                    for (int32_t c = 0; c < (short_tail ? chunks - 1 : chunks); ++c) push(row, 64 * c, 0);
-                    if (!short_tail) continue;
-                    const bool inner = y > 0 && y < g.ny - 1 && z > 0 && z < g.nz - 1;
-                    if (!inner) {
-                        push(row, x_tail, 0);
-                    } else if (pending < 0) {
-                        pending = row;
-                    } else {
-                        push(pending, x_tail, row - pending);
-                        pending = -1;
-                    }
-                }
-            if (pending >= 0) push(pending, x_tail, 0);
-            if (tiles.size() / 4 > 0x1fffffffull) return fail(CLBM_EINVAL, "batch has more than 2^29 row items");
-        }
-        total = tiles.size() / 4;
-    } else {
-        if (total > 0x7fffffffull) return fail(CLBM_EINVAL, "batch has more than 2^31 tiles");
-        tiles.resize(total);
-        for (int i = 0; i < b->count; ++i) {
-            const uint64_t n = (uint64_t)inst[i].chunks * (uint64_t)b->geom[i].nz;
-            std::fill(tiles.begin() + inst[i].tile0, tiles.begin() + inst[i].tile0 + n, i);
-        }
-    }
+    if (total > 0x7fffffffull) return fail(CLBM_EINVAL, "batch has more than 2^31 tiles");
+    tiles.resize(total);
+    for (int i = 0; i < b->count; ++i)
+        std::fill(tiles.begin() + inst[i].tile0, i + 1 < b->count ? tiles.begin() + inst[i + 1].tile0 : tiles.end(), i);
     const size_t vals = tiles.size();
     if (vals > b->tile_cap) {
         if (b->d_tiles) (void)hipFree(b->d_tiles);
@@ -644,12 +480,14 @@ clbm_status clbm_batch_create(const clbm_params *inst, int32_t count, void *pool
     b->pool[0] = pool_a;
     b->pool[1] = pool_b;
     b->bytes_each = bytes_each;
-    b->cfg.bx = max_threads(b);
+    // row layout: 256 threads (64-cavity mix, FP32: 617 us per step, 650 at 512, 669 at 128; FP16, bound by
+    // arithmetic, 411 at 512, 418 at 256)
+    b->cfg.bx = b->rows && b->storage != CLBM_F16_DEV ? 256 : max_threads(b);
     b->cfg.by = 1;
     b->cfg.blocks_per_cu = 1024;    // capped at one item per wave (row layout) or one tile per workgroup
     b->cfg.graph_steps = 20;
     b->cfg.nt_stores = 0;
-    b->cfg.passes = 0;          // one row run per wave item: faster than packed items on the 64-cavity mix
+    b->cfg.passes = 0;
     b->num_cus = 256;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&

@@ -304,7 +304,7 @@ __device__ inline T clampv(T v, T lo, T hi) { return fmin(fmax(v, lo), hi); }
 // and the final clamp of tau gives the clipped viscosity, as required.
 // NI: fixed Newton steps of the FP32 iteration (FP64 iterates to convergence).
 template <typename T, int NI = NewtonTol<T>::maxit>
-__device__ inline T solve_tau(const Relax<T> &p, T rho, T a, T b) {
+__device__ __forceinline__ T solve_tau(const Relax<T> &p, T rho, T a, T b) {
     if (p.newtonian) return clampv(T(0.5) + p.three_K * fast_rcp(rho), p.tau_min, p.tau_max);
     const T q0 = a + b;
     if (q0 == T(0)) {
@@ -410,7 +410,7 @@ __device__ inline void add_raw_moment_change(T d[Q], T dR0, T dRx, T dRy, T dRz,
 // order of the incoming state are needed.
 // ---------------------------------------------------------------------------
 template <typename T, bool Forced, int NI = NewtonTol<T>::maxit>
-__device__ inline void collide_unit_high(T d[Q], const Relax<T> &p, T *omega_out) {
+__device__ __forceinline__ void collide_unit_high(T d[Q], const Relax<T> &p, T *omega_out) {
     const T third = T(1) / T(3);
     // raw moments of the deviations (the rest part contributes 1, 0, 1/3, 0)
     const T exy_p = d[7] + d[10], exy_m = d[8] + d[9];
@@ -534,7 +534,7 @@ __device__ inline void collide_unit_high(T d[Q], const Relax<T> &p, T *omega_out
 // state and the full source (central moments (0, F, 0, ...)) is added.
 // ---------------------------------------------------------------------------
 template <typename T, bool Forced, int NI = NewtonTol<T>::maxit>
-__device__ inline void collide_ghat(T d[Q], const Relax<T> &p, T *omega_out) {
+__device__ __forceinline__ void collide_ghat(T d[Q], const Relax<T> &p, T *omega_out) {
     const T third = T(1) / T(3);
     // raw moments of the deviations (rest parts: 1, 1/3 on the diagonal, 1/9
     // on xxyy, xxzz, yyzz, zero elsewhere)
@@ -727,7 +727,7 @@ __device__ inline void collide_ghat(T d[Q], const Relax<T> &p, T *omega_out) {
 // Unforced only.
 // ---------------------------------------------------------------------------
 template <typename T, int NI = NewtonTol<T>::maxit>
-__device__ inline void collide_srt(T d[Q], const Relax<T> &p, T *omega_out) {
+__device__ __forceinline__ void collide_srt(T d[Q], const Relax<T> &p, T *omega_out) {
     const T third = T(1) / T(3);
     const T exy_p = d[7] + d[10], exy_m = d[8] + d[9];
     const T exz_p = d[11] + d[14], exz_m = d[12] + d[13];

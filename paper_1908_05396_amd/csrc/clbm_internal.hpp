@@ -57,7 +57,7 @@ hipError_t launch_check_flags(const uint8_t *flags, int64_t n, double *bad, hipS
 // paper's printed changes of moments g4..g18 with f~ = f + K.g.
 // Route 2: the single-relaxation-time comparison model (unforced only).
 template <typename T, bool Forced, int Route, int NI = NewtonTol<T>::maxit>
-__device__ inline void collide(T d[Q], const Relax<T> &p, T *omega_out) {
+__device__ __forceinline__ void collide(T d[Q], const Relax<T> &p, T *omega_out) {
     if constexpr (Route == 0) {
         collide_unit_high<T, Forced, NI>(d, p, omega_out);
     } else if constexpr (Route == 1) {

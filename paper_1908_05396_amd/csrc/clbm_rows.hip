@@ -7,7 +7,7 @@
 // over the whole buffer, which keeps the DRAM page and bank traffic of
 // neighbouring waves together.
 //
-//   stream_collide_flat   one thread per node, 64 consecutive nodes per wave,
+//   stream_collide_rows_flat   one thread per node, 64 consecutive nodes per wave,
 //                         per-lane source addresses: no idle lanes at any
 //                         width, no second launch or second round of loads for
 //                         the faces.
@@ -19,74 +19,6 @@
 #include "clbm_rows.hpp"
 
 namespace clbm {
-
-namespace {
-
-// Pull gather of 64 consecutive nodes with the full wall logic (Eq. cascaded
-// streaming with the rules of Sec. 4) on every lane: periodic wrap, half-way
-// bounce-back, moving lid.  Which value a direction reads - the source's, or
-// the node's own opposite population beyond a wall - is a select on its
-// address, so the 19 loads go out together and the wave waits for memory once;
-// the lid terms are added afterwards, in waves that touch the lid.
-//
-// `own` is the byte offset from A of the node's own row group plus its x, and
-// every source lies within 32 bits of it: loads go through one descriptor
-// that starts K = layer + row + one value before A (no access falls before A),
-// which keeps the lane offsets positive.  Far: the lattice itself is larger;
-// lanes that pull across a periodic z face then address in 64 bits.
-//
-// Waves without a face node could use one lane offset and 19 scalar ones.
-// Their loads then issue back to back, which the memory serves worse than
-// loads a few instructions apart: 200 x 190 x 220 FP32 304 us per step with
-// that path against 250 without, 256^3 FP16 233 against 227; not kept.
-template <typename S, typename T, int LdAux, bool Far>
-__device__ inline void gather_flat(const S *__restrict__ A, uint32_t own, const Geom &g, const Relax<T> &p, int x,
-                                   int y, int z, T (&d)[Q]) {
-    constexpr uint32_t es = sizeof(S);
-    const uint32_t run = (uint32_t)g.nx * es, row = Q * run, layer = row * (uint32_t)g.ny, K = layer + row + es;
-    const bool lo[3] = {x == 0, y == 0, z == 0};
-    const bool hi[3] = {x == g.nx - 1, y == g.ny - 1, z == g.nz - 1};
-    const bool per[3] = {g.px != 0, g.py != 0, g.pz != 0};
-    // per axis, index c + 1 for c = -1, 0, +1: byte distance to the (wrapped)
-    // source (Far: lanes wrapping in z read their own layer here and are redone below)
-    const uint32_t wrap = Far ? layer : layer * (uint32_t)g.nz;
-    const uint32_t dx[3] = {hi[0] ? es - run : es, 0u, lo[0] ? run - es : 0u - es};
-    const uint32_t dy[3] = {hi[1] ? row - layer : row, 0u, lo[1] ? layer - row : 0u - row};
-    const uint32_t dz[3] = {hi[2] ? layer - wrap : layer, 0u, lo[2] ? wrap - layer : 0u - layer};
-    auto ghost = [&](int axis, int c) { return c != 0 && !per[axis] && (c == 1 ? lo[axis] : hi[axis]); };
-    const __amdgpu_buffer_rsrc_t rsrc = row_rsrc((const char *)A - K, 0xFFFFFFFFu);
-    const uint32_t self = own + K;
-#pragma unroll
-    for (int a = 0; a < Q; ++a) {
-        const bool wall = ghost(0, cx(a)) | ghost(1, cy(a)) | ghost(2, cz(a));
-        const uint32_t src = self + dx[cx(a) + 1] + dy[cy(a) + 1] + dz[cz(a) + 1];
-        d[a] = (T)RawBits<S>::template load<LdAux>(rsrc, wall ? self + (uint32_t)(opp(a) - a) * run : src,
-                                                   (uint32_t)a * run);
-    }
-    const int m = g.lid_mask;
-    auto lid = [&](int axis, int c) {
-        return c != 0 && (c == 1 ? ((m >> (2 * axis)) & 1) && lo[axis] : ((m >> (2 * axis + 1)) & 1) && hi[axis]);
-    };
-    const bool any = lid(0, 1) | lid(0, -1) | lid(1, 1) | lid(1, -1) | lid(2, 1) | lid(2, -1);
-    if (__builtin_amdgcn_ballot_w64(any) != 0) {
-#pragma unroll
-        for (int a = 1; a < Q; ++a)
-            d[a] = wall_value<T>(d[a], p, a, lid(0, cx(a)) | lid(1, cy(a)) | lid(2, cz(a)));
-    }
-    if constexpr (Far) {
-        if (per[2] && (lo[2] || hi[2])) {
-#pragma unroll
-            for (int a = 1; a < Q; ++a) {
-                if (cz(a) == 0 || !(cz(a) == 1 ? lo[2] : hi[2]) || ghost(0, cx(a)) || ghost(1, cy(a))) continue;
-                const int64_t to = (int64_t)(int32_t)(dx[cx(a) + 1] + dy[cy(a) + 1]) + (int64_t)a * run +
-                                   cz(a) * (int64_t)(g.nz - 1) * (int64_t)layer;
-                d[a] = (T)Conv<S, T>::load(*(const S *)((const char *)A + own + to));
-            }
-        }
-    }
-}
-
-}  // namespace
 
 // One thread per node, 64 consecutive nodes (x fastest, across rows and
 // layers) per wave, so no lane is idle at any width.
@@ -101,7 +33,7 @@ __device__ inline void gather_flat(const S *__restrict__ A, uint32_t own, const 
 // one workgroup: 200 x 190 x 220 FP32 250 against 375 us.
 template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route, bool Far>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
-stream_collide_flat_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, FlatGrid L) {
+stream_collide_rows_flat_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, FlatGrid L) {
     uint32_t b = blockIdx.x;
     if (L.remap && b < L.aligned) b = (b & 7u) * (L.aligned >> 3) + (b >> 3);
     const uint32_t i = b * blockDim.x + threadIdx.x;
@@ -128,9 +60,9 @@ stream_collide_rows_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, R
     const int y = (int)(ri % (uint32_t)g.ny), z = (int)(ri / (uint32_t)g.ny);
     T d[Q];
     if (y >= 1 && y <= g.ny - 2 && z >= 1 && z <= g.nz - 2)
-        row_gather<S, T, LdAux, false, false, XGroupRows<S>::value>(A, g, p, x, y, z, d);
+        row_gather<S, T, LdAux, false, XGroupRows<S>::value>(A, g, p, x, y, z, d);
     else
-        row_gather<S, T, LdAux, true, false, XGroupRows<S>::value>(A, g, p, x, y, z, d);
+        row_gather<S, T, LdAux, true, XGroupRows<S>::value>(A, g, p, x, y, z, d);
     collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
     const uint32_t node = (uint32_t)x + (uint32_t)g.nx * ri;
     row_store<S, T, StAux>(B, g, x, y, z, d, p.sr != 0, sr_base(node, p.step));
@@ -161,10 +93,10 @@ static hipError_t launch_rows_k(const S *a, S *b, const Geom &g, const Relax<T> 
         L.aligned = blocks & ~7u;
         L.remap = c.xcd_remap;
         if (near && !(far && prefer_far))
-            hipLaunchKernelGGL((stream_collide_flat_kernel<S, T, Forced, LdAux, StAux, Route, false>), dim3(blocks),
+            hipLaunchKernelGGL((stream_collide_rows_flat_kernel<S, T, Forced, LdAux, StAux, Route, false>), dim3(blocks),
                                dim3(threads), 0, st, a, b, g, p, L);
         else
-            hipLaunchKernelGGL((stream_collide_flat_kernel<S, T, Forced, LdAux, StAux, Route, true>), dim3(blocks),
+            hipLaunchKernelGGL((stream_collide_rows_flat_kernel<S, T, Forced, LdAux, StAux, Route, true>), dim3(blocks),
                                dim3(threads), 0, st, a, b, g, p, L);
         return hipGetLastError();
     }

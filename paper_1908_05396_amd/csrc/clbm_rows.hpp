@@ -112,43 +112,30 @@ inline uint32_t face_rows(const Geom &g, int threads, RowGrid &R) {
 // slower that way and keeps the per-direction path.
 template <typename S> struct XGroupRows { static constexpr bool value = std::is_same<S, float>::value; };
 
-// A wave may serve two rows r and r + k of one lattice as two halves (the
-// short tails of two rows in a batch): every run the second half reads or
-// writes lies k row groups after the first half's, the same byte distance D
-// for all 19 directions, so its lanes add D to their offsets (`Shift::lane`)
-// and every descriptor's range grows by D (`Shift::range`).
-struct Shift {
-    uint32_t lane;      // bytes added to this lane's offsets (0 or D)
-    uint32_t range;     // D: added to every descriptor's range (uniform)
-};
-
 // Pull of node x of row (y, z) with the wall rules into d; y and z uniform
-// over the wave (or over each half, Pair); Face: the row may lie on a y or z
-// face; XGroup: the x-face bounce-back loads of a wave issued together (below).
+// over the wave; Face: the row may lie on a y or z face; XGroup: the x-face
+// bounce-back loads of a wave issued together (below).
 //
 // Nine source rows (one per e_y, e_z), each with a descriptor whose base lies
 // one value before the row group; direction a's run at the scalar offset
 // a nx.  The lane offset selects x - cx(a) + 1, wrapped on a periodic x axis;
 // it is shared by the directions of one cx.
-template <typename S, typename T, int LdAux, bool Face, bool Pair = false, bool XGroup = false>
+template <typename S, typename T, int LdAux, bool Face, bool XGroup = false>
 __device__ inline void row_gather(const S *__restrict__ A, const Geom &g, const Relax<T> &p, int x, int y, int z,
-                                  T (&d)[Q], Shift sh = Shift{0u, 0u}) {
-    static_assert(!(Pair && Face), "paired rows lie off the y and z faces");
+                                  T (&d)[Q]) {
     constexpr uint32_t es = sizeof(S);
     // On a non-periodic x face the source column x - cx(a) = -1 or nx is a
     // ghost, whose value the x-face rule below supplies: those lanes take an
     // offset beyond every descriptor's range, so the load returns 0 without
     // touching memory (and the cache line past the run is not fetched for
     // them).  (the lengths pass through readfirstlane so that the compiler
-    // keeps them in scalar registers; a second half's offsets, past D, and the
-    // run offsets stay below 2^31 bytes)
+    // keeps them in scalar registers; run offsets stay below 2^31 bytes)
     const uint32_t run = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
-    const uint32_t range = (uint32_t)(Q * run) + 2 * es + (Pair ? sh.range : 0u);
-    const uint32_t add = Pair ? sh.lane : 0u;
+    const uint32_t range = (uint32_t)(Q * run) + 2 * es;
     constexpr uint32_t outside = 0x80000000u;
-    const uint32_t o0 = (uint32_t)(x + 1) * es + add;
-    const uint32_t op = (x == 0 ? (g.px ? run : outside) : (uint32_t)x * es) + add;                  // cx = +1
-    const uint32_t om = (x == g.nx - 1 ? (g.px ? es : outside) : (uint32_t)(x + 2) * es) + add;      // cx = -1
+    const uint32_t o0 = (uint32_t)(x + 1) * es;
+    const uint32_t op = x == 0 ? (g.px ? run : outside) : (uint32_t)x * es;                  // cx = +1
+    const uint32_t om = x == g.nx - 1 ? (g.px ? es : outside) : (uint32_t)(x + 2) * es;      // cx = -1
     auto lane_off = [&](int a) { return cx(a) == 1 ? op : (cx(a) == -1 ? om : o0); };
     const int64_t row = g.row, layer = (int64_t)g.ny * g.row;
     const S *own = A + ((int64_t)z * layer + (int64_t)y * row) - 1;
@@ -251,7 +238,7 @@ __device__ inline void row_gather(const S *__restrict__ A, const Geom &g, const 
 // rounded in the store itself with the seeds of round_state (sr_base =
 // sr_base(node, step)).
 template <typename S, typename T, int StAux>
-__device__ inline void row_store_at(__amdgpu_buffer_rsrc_t out, uint32_t lane, uint32_t run, const T (&d)[Q], bool sr,
+__device__ __forceinline__ void row_store_at(__amdgpu_buffer_rsrc_t out, uint32_t lane, uint32_t run, const T (&d)[Q], bool sr,
                                     uint32_t seed_base) {
     if constexpr (std::is_same<S, __half>::value) {
         if (sr) {
@@ -274,43 +261,79 @@ __device__ inline void row_store_at(__amdgpu_buffer_rsrc_t out, uint32_t lane, u
     for (int a = 0; a < Q; ++a) RawBits<S>::template store<StAux>(out, lane, d[a], (uint32_t)a * run);
 }
 
-// Store at node x of row (y, z) (y, z uniform; Pair: the second half's lanes
-// shifted as in row_gather).
-template <typename S, typename T, int StAux, bool Pair = false>
+// Store at node x of row (y, z) (y, z uniform).
+template <typename S, typename T, int StAux>
 __device__ inline void row_store(S *__restrict__ B, const Geom &g, int x, int y, int z, const T (&d)[Q],
-                                 bool sr = false, uint32_t seed_base = 0, Shift sh = Shift{0u, 0u}) {
+                                 bool sr = false, uint32_t seed_base = 0) {
     constexpr uint32_t es = sizeof(S);
     const uint32_t run = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
     const __amdgpu_buffer_rsrc_t out =
-        row_rsrc(B + ((int64_t)z * g.ny + y) * g.row, (uint32_t)Q * run + (Pair ? sh.range : 0u));
-    row_store_at<S, T, StAux>(out, (uint32_t)x * es + (Pair ? sh.lane : 0u), run, d, sr, seed_base);
+        row_rsrc(B + ((int64_t)z * g.ny + y) * g.row, (uint32_t)Q * run);
+    row_store_at<S, T, StAux>(out, (uint32_t)x * es, run, d, sr, seed_base);
 }
 
-// One step of node x of row (y, z): gather, collide, store; `step` is the
-// index of the collision (keys the stochastic rounding of FP16 storage).
-template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route, bool Face, bool XGroup = false>
-__device__ inline void row_step(const S *__restrict__ A, S *__restrict__ B, const Geom &g, const Relax<T> &p, int x,
-                                int y, int z, uint32_t step) {
-    T d[Q];
-    row_gather<S, T, LdAux, Face, false, XGroup>(A, g, p, x, y, z, d);
-    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    const uint32_t node = (uint32_t)x + (uint32_t)g.nx * ((uint32_t)y + (uint32_t)g.ny * (uint32_t)z);
-    row_store<S, T, StAux>(B, g, x, y, z, d, p.sr != 0, sr_base(node, step));
-}
-
-// The same step for a wave serving two inner rows r = y + ny z (lanes with
-// hi false) and r + k (lanes with hi true), each lane at column x of its row.
-template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route>
-__device__ inline void row_step_pair(const S *__restrict__ A, S *__restrict__ B, const Geom &g, const Relax<T> &p,
-                                     int x, int y, int z, uint32_t k, bool hi, uint32_t step) {
+// Pull gather of 64 consecutive nodes with the full wall logic (Eq. cascaded
+// streaming with the rules of Sec. 4) on every lane: periodic wrap, half-way
+// bounce-back, moving lid.  Which value a direction reads - the source's, or
+// the node's own opposite population beyond a wall - is a select on its
+// address, so the 19 loads go out together and the wave waits for memory once;
+// the lid terms are added afterwards, in waves that touch the lid.
+//
+// `own` is the byte offset from A of the node's own row group plus its x, and
+// every source lies within 32 bits of it: loads go through one descriptor
+// that starts K = layer + row + one value before A (no access falls before A),
+// which keeps the lane offsets positive.  Far: the lattice itself is larger;
+// lanes that pull across a periodic z face then address in 64 bits.
+//
+// Waves without a face node could use one lane offset and 19 scalar ones.
+// Their loads then issue back to back, which the memory serves worse than
+// loads a few instructions apart: 200 x 190 x 220 FP32 304 us per step with
+// that path against 250 without, 256^3 FP16 233 against 227; not kept.
+template <typename S, typename T, int LdAux, bool Far>
+__device__ __forceinline__ void gather_flat(const S *__restrict__ A, uint32_t own, const Geom &g, const Relax<T> &p, int x,
+                                   int y, int z, T (&d)[Q]) {
     constexpr uint32_t es = sizeof(S);
-    const uint32_t D = k * (uint32_t)g.row * es;
-    const Shift sh{hi ? D : 0u, D};
-    T d[Q];
-    row_gather<S, T, LdAux, false, true, XGroupRows<S>::value>(A, g, p, x, y, z, d, sh);
-    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    const uint32_t node = (uint32_t)x + (uint32_t)g.nx * ((uint32_t)y + (uint32_t)g.ny * (uint32_t)z + (hi ? k : 0u));
-    row_store<S, T, StAux, true>(B, g, x, y, z, d, p.sr != 0, sr_base(node, step), sh);
+    const uint32_t run = (uint32_t)g.nx * es, row = Q * run, layer = row * (uint32_t)g.ny, K = layer + row + es;
+    const bool lo[3] = {x == 0, y == 0, z == 0};
+    const bool hi[3] = {x == g.nx - 1, y == g.ny - 1, z == g.nz - 1};
+    const bool per[3] = {g.px != 0, g.py != 0, g.pz != 0};
+    // per axis, index c + 1 for c = -1, 0, +1: byte distance to the (wrapped)
+    // source (Far: lanes wrapping in z read their own layer here and are redone below)
+    const uint32_t wrap = Far ? layer : layer * (uint32_t)g.nz;
+    const uint32_t dx[3] = {hi[0] ? es - run : es, 0u, lo[0] ? run - es : 0u - es};
+    const uint32_t dy[3] = {hi[1] ? row - layer : row, 0u, lo[1] ? layer - row : 0u - row};
+    const uint32_t dz[3] = {hi[2] ? layer - wrap : layer, 0u, lo[2] ? wrap - layer : 0u - layer};
+    auto ghost = [&](int axis, int c) { return c != 0 && !per[axis] && (c == 1 ? lo[axis] : hi[axis]); };
+    const __amdgpu_buffer_rsrc_t rsrc = row_rsrc((const char *)A - K, 0xFFFFFFFFu);
+    const uint32_t self = own + K;
+#pragma unroll
+    for (int a = 0; a < Q; ++a) {
+        const bool wall = ghost(0, cx(a)) | ghost(1, cy(a)) | ghost(2, cz(a));
+        const uint32_t src = self + dx[cx(a) + 1] + dy[cy(a) + 1] + dz[cz(a) + 1];
+        d[a] = (T)RawBits<S>::template load<LdAux>(rsrc, wall ? self + (uint32_t)(opp(a) - a) * run : src,
+                                                   (uint32_t)a * run);
+    }
+    const int m = g.lid_mask;
+    auto lid = [&](int axis, int c) {
+        return c != 0 && (c == 1 ? ((m >> (2 * axis)) & 1) && lo[axis] : ((m >> (2 * axis + 1)) & 1) && hi[axis]);
+    };
+    const bool any = lid(0, 1) | lid(0, -1) | lid(1, 1) | lid(1, -1) | lid(2, 1) | lid(2, -1);
+    if (__builtin_amdgcn_ballot_w64(any) != 0) {
+#pragma unroll
+        for (int a = 1; a < Q; ++a)
+            d[a] = wall_value<T>(d[a], p, a, lid(0, cx(a)) | lid(1, cy(a)) | lid(2, cz(a)));
+    }
+    if constexpr (Far) {
+        if (per[2] && (lo[2] || hi[2])) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a) {
+                if (cz(a) == 0 || !(cz(a) == 1 ? lo[2] : hi[2]) || ghost(0, cx(a)) || ghost(1, cy(a))) continue;
+                const int64_t to = (int64_t)(int32_t)(dx[cx(a) + 1] + dy[cy(a) + 1]) + (int64_t)a * run +
+                                   cz(a) * (int64_t)(g.nz - 1) * (int64_t)layer;
+                d[a] = (T)Conv<S, T>::load(*(const S *)((const char *)A + own + to));
+            }
+        }
+    }
 }
 
 }  // namespace clbm
