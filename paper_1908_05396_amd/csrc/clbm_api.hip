@@ -65,12 +65,12 @@ static void default_fusion(const clbm_params *p, StepLaunch *c) {
 }
 
 // Default block shape, workgroup order and store hint (measured on MI355X).
-static void default_launch(const clbm_params *p, bool in_place, size_t bytes, StepLaunch *c) {
+static void default_launch(const clbm_params *p, size_t bytes, StepLaunch *c) {
     const bool rows = p->layout == CLBM_LAYOUT_ROWS;
     c->xcd_remap = rows ? 1 : 0;    // rows: XCD-contiguous order is 1-6% faster than the dispatch order at 512^3
     c->nt_loads = 0;
     c->nt_stores = 1;               // streaming stores: the new state is not re-read this step
-    if (rows && !in_place) {
+    if (rows) {
         // Workgroups of 256 consecutive nodes; of 64 below 65 536 nodes, so
         // that every compute unit gets one (8 x 32 x 8 FP64 5.0 against 5.5 us).
         // FP32 states from 4 GiB whose rows are not whole 64-byte pieces: a
@@ -90,14 +90,12 @@ static void default_launch(const clbm_params *p, bool in_place, size_t bytes, St
         c->nt_stores = pieces && 2 * bytes > ((size_t)256 << 20);
         return;
     }
-    // up to 256 threads along x (whole 64-wide waves), rows stacked along y
-    // when the lattice is narrow (rows: one lattice row per block; FP64 up to 128 wide)
+    // planes: up to 256 threads along x (whole 64-wide waves), rows stacked
+    // along y when the lattice is narrow
     int bx = p->nx >= 64 ? 64 * (p->nx / 64) : p->nx;
     if (bx > 256) bx = 256;
-    if (rows && p->storage == CLBM_F64 && bx > 128) bx = 128;
     int by = 1;
-    const int threads = (rows && p->nx >= 64) ? bx : 256;
-    while (bx * by * 2 <= threads && by * 2 <= p->ny) by *= 2;
+    while (bx * by * 2 <= 256 && by * 2 <= p->ny) by *= 2;
     c->bx = bx;
     c->by = by;
 }
@@ -194,7 +192,7 @@ static clbm_status create_common(const clbm_params *p, void *pop_a, void *pop_b,
     h->buf[1] = pop_b;
     h->bytes_each = bytes_each;
     h->cur = 0;
-    default_launch(p, in_place, need, &h->launch);
+    default_launch(p, need, &h->launch);
     default_fusion(p, &h->launch);
 
     const int64_t N = (int64_t)p->nx * p->ny * p->nz;

@@ -123,99 +123,100 @@ __global__ void __launch_bounds__(256) store_plain_kernel(const double *__restri
 }
 
 // ---------------------------------------------------------------------------
-// The same pair of steps on the row layout (waves of 64 x of one row; scalar
-// bases per direction as in the two-buffer row kernels).
+// The same pair of steps on the row layout, in waves of 64 consecutive nodes
+// with the full wall logic by address selects (FlatNode).
 // ---------------------------------------------------------------------------
 // Even step: the node's own 19 runs, collided, each value stored in the run
 // of the opposite direction.
-template <typename S, typename T, bool Forced, int Route>
+template <typename S, typename T, bool Forced, int Route, bool Far>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
-aa_even_rows_kernel(S *__restrict__ A, Geom g, Relax<T> p, RowGrid R) {
-    constexpr uint32_t es = sizeof(S);
-    int x;
-    uint32_t ri;
-    if (!row_of(R, x, ri) || x >= g.nx) return;
-    // one descriptor for the row group; the run of direction a at scalar offset a nx
-    const uint32_t run = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
-    const __amdgpu_buffer_rsrc_t own = row_rsrc(A + (int64_t)ri * g.row, (uint32_t)Q * run);
-    const uint32_t lane = (uint32_t)x * es;
+aa_even_flat_kernel(S *__restrict__ A, Geom g, Relax<T> p, FlatGrid L) {
+    const FlatLane<S, Far> k(g, L);
+    if (k.i >= (uint32_t)g.n) return;
+    const uint32_t run = (uint32_t)g.nx * (uint32_t)sizeof(S);
+    const __amdgpu_buffer_rsrc_t own = row_rsrc(A + k.r0 * g.row, 0xFFFFFFFFu);
     T d[Q];
 #pragma unroll
-    for (int a = 0; a < Q; ++a) d[a] = (T)RawBits<S>::template load<0>(own, lane, (uint32_t)a * run);
+    for (int a = 0; a < Q; ++a) d[a] = (T)RawBits<S>::template load<0>(own, k.own, (uint32_t)a * run);
     collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    round_state<S, T>(d, p, (uint32_t)x + (uint32_t)g.nx * ri, p.step);
+    round_state<S, T>(d, p, k.i, p.step);
 #pragma unroll
-    for (int a = 0; a < Q; ++a) RawBits<S>::template store<EvenStAux>(own, lane, d[a], (uint32_t)opp(a) * run);
+    for (int a = 0; a < Q; ++a) RawBits<S>::template store<EvenStAux>(own, k.own, d[a], (uint32_t)opp(a) * run);
 }
 
-// Odd step at node x of an inner row (y, z off the y and z faces): every
-// source and target row lies inside the lattice.  Pull: f~_a(x - e_a) from
-// run opp(a) of the source row (base one value before the run, lane offset
-// x - cx(a) + 1, wrapped on a periodic x axis; the lanes of a non-periodic x
-// face read a neighbouring run there and are redone).  Push: f~_a(x) to run a
-// of the target row at x + cx(a); on a non-periodic x face the lanes whose
-// target column is a ghost skip that store and the bounce-back below stores
-// into the node's own row group instead.
-template <typename S, typename T, bool Forced, int Route>
-__device__ inline void aa_odd_row(S *__restrict__ A, const Geom &g, const Relax<T> &p, int x, int y, int z) {
-    constexpr uint32_t es = sizeof(S);
-    const int64_t r = (int64_t)z * g.ny + y;
-    const uint32_t prange = __builtin_amdgcn_readfirstlane((uint32_t)(g.nx + 2) * es);
-    const uint32_t srange = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
-    const bool xl = x == 0, xr = x == g.nx - 1;
-    // pull offsets from the base one value before the run; a ghost source
-    // column of a non-periodic x face (replaced below) takes an offset beyond
-    // the descriptor's range, so its load touches no memory
-    constexpr uint32_t outside = 0x80000000u;
-    const uint32_t o0 = (uint32_t)(x + 1) * es;
-    const uint32_t op = xl ? (g.px ? prange - 2 * es : outside) : (uint32_t)x * es;       // cx = +1: source x - 1
-    const uint32_t om = xr ? (g.px ? es : outside) : (uint32_t)(x + 2) * es;              // cx = -1: source x + 1
-    // push offsets from the run start (kept inside the run on the lanes that skip the store)
-    const uint32_t t0 = (uint32_t)x * es;
-    const uint32_t tp = xr ? (g.px ? 0u : t0) : (uint32_t)(x + 1) * es;          // cx = +1: target x + 1
-    const uint32_t tm = xl ? (g.px ? srange - es : t0) : (uint32_t)(x - 1) * es; // cx = -1: target x - 1
-    auto pull_off = [&](int a) { return cx(a) == 1 ? op : (cx(a) == -1 ? om : o0); };
-    auto push_off = [&](int a) { return cx(a) == 1 ? tp : (cx(a) == -1 ? tm : t0); };
-    // pulls: one descriptor per source row group (from one value before it),
-    // the run opp(a) at a scalar offset; every address lies inside the group
-    const uint32_t run = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
-    const uint32_t grange = (uint32_t)Q * run + 2 * es;
+// Odd step.  Pull: f~_a(x - e_a) from run opp(a) of the source, or beyond a
+// wall the node's own f~_opp(a), which the even step left in run a.  Push:
+// f~_a(x) to run a of x + e_a, or beyond a wall, with the lid term of the
+// opposite direction, into the node's own run opp(a).  The target of a is the
+// source of b = opp(a), so the store of a goes to exactly the address that
+// direction b was loaded from.
+//
+// Bound: HBM, whose rate the pair of misaligned reads and writes keeps below the
+// two-buffer step's: 250 x 240 x 230 FP32 414 us per step, 5.1 TB/s (510 with
+// one wave per run of a row, the x faces apart and the y and z faces in a second
+// launch with a wait per direction).
+template <typename S, typename T, bool Forced, int Route, bool Far>
+__global__ void __launch_bounds__(MaxThreads<T>::value)
+aa_odd_flat_kernel(S *__restrict__ A, Geom g, Relax<T> p, FlatGrid L) {
+    const FlatLane<S, Far> k(g, L);
+    if (k.i >= (uint32_t)g.n) return;
+    S *Aw = A + k.r0 * g.row;
     T d[Q];
+    auto far = [&](const FlatNode<S, Far> &f, int a) {
+        return (S *)((char *)Aw + k.own + f.wrapped(g, a) + (int64_t)opp(a) * f.run);
+    };
+    auto offset = [&](const FlatNode<S, Far> &f, int a) {
+        return f.wall(a) ? f.self + (uint32_t)(a - opp(a)) * f.run : f.source(a);
+    };
+    {
+        const FlatNode<S, Far> f(g, k.own, k.x, k.y, k.z);
+        const __amdgpu_buffer_rsrc_t rsrc = f.rsrc(Aw);
 #pragma unroll
-    for (int a = 0; a < Q; ++a) {
-        const S *base = A + (r - cy(a) - (int64_t)cz(a) * g.ny) * g.row - 1;
-        d[a] = (T)RawBits<S>::template load<0>(row_rsrc(base, grange), pull_off(a), (uint32_t)opp(a) * run);
-    }
-    const bool xwall = !g.px && (xl || xr);
-    if (xwall) {
-        // source column is a ghost: the node's own f~_opp(a), left in run a by the even step
+        for (int a = 0; a < Q; ++a)
+            d[a] = (T)RawBits<S>::template load<0>(rsrc, offset(f, a), (uint32_t)opp(a) * f.run);
+        if (f.wave_touches_lid()) {
 #pragma unroll
-        for (int a = 1; a < Q; ++a)
-            if ((xl && cx(a) == 1) || (xr && cx(a) == -1))
-                d[a] = wall_value<T>((T)Conv<S, T>::load(A[elem(g, a, x, y, z)]), p, a,
-                                     (g.lid_mask & (cx(a) == 1 ? 1 : 2)) != 0);
+            for (int a = 1; a < Q; ++a) d[a] = wall_value<T>(d[a], p, a, f.lid(a));
+        }
+        if constexpr (Far) {
+            if (g.pz && (f.lo[2] || f.hi[2])) {
+#pragma unroll
+                for (int a = 1; a < Q; ++a)
+                    if (cz(a) != 0 && f.wraps(a)) d[a] = (T)Conv<S, T>::load(*far(f, a));
+            }
+        }
     }
     collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    round_state<S, T>(d, p, (uint32_t)x + (uint32_t)g.nx * (uint32_t)r, p.step);
+    round_state<S, T>(d, p, k.i, p.step);
+    // the addresses once more: kept over the collision they cost 20 registers
+    // (84 instead of 64 VGPRs in FP32)
+    uint32_t own = k.own;
+    int x = k.x, y = k.y, z = k.z;
+    asm volatile("" : "+v"(own), "+v"(x), "+v"(y), "+v"(z));
+    const FlatNode<S, Far> f(g, own, x, y, z);
+    const __amdgpu_buffer_rsrc_t rsrc = f.rsrc(Aw);
+    if (f.wave_touches_lid()) {
+#pragma unroll
+        for (int a = 1; a < Q; ++a) d[a] = wall_value<T>(d[a], p, opp(a), f.lid(opp(a)));
+    }
 #pragma unroll
     for (int a = 0; a < Q; ++a) {
-        if (xwall && ((xl && cx(a) == -1) || (xr && cx(a) == 1))) continue;
-        S *base = A + (r + cy(a) + (int64_t)cz(a) * g.ny) * g.row + (int64_t)a * g.nx;
-        RawBits<S>::template store<OddStAux>(row_rsrc(base, srange), push_off(a), d[a]);
+        const int b = opp(a);
+        // (Far: a lane that wraps in z points beyond the descriptor's range, so the store is dropped)
+        const uint32_t o = Far && f.wraps(b) ? 0x80000000u : offset(f, b);
+        RawBits<S>::template store<OddStAux>(rsrc, o, d[a], (uint32_t)a * f.run);
     }
-    if (xwall) {
-        // target column is a ghost: back into the node's own run opp(a), with
-        // the lid term of direction opp(a): the value the pull rule gives next step
+    if constexpr (Far) {
+        if (g.pz && (f.lo[2] || f.hi[2])) {
 #pragma unroll
-        for (int a = 1; a < Q; ++a)
-            if ((xl && cx(a) == -1) || (xr && cx(a) == 1))
-                A[elem(g, opp(a), x, y, z)] =
-                    Conv<S, T>::store(wall_value<T>(d[a], p, opp(a), (g.lid_mask & (cx(a) == -1 ? 1 : 2)) != 0));
+            for (int a = 1; a < Q; ++a)
+                if (cz(a) != 0 && f.wraps(opp(a))) *far(f, opp(a)) = Conv<S, T>::store(d[a]);
+        }
     }
 }
 
 // Even and odd steps at one node with the full wall rule per lane, in either
-// layout (face rows of the row kernels, and narrow lattices).
+// layout (layers beyond the reach of 32-bit offsets).
 template <typename S, typename T, bool Forced, int Route>
 __device__ inline void aa_even_any(S *__restrict__ A, const Geom &g, const Relax<T> &p, int x, int y, int z) {
     T d[Q];
@@ -252,28 +253,6 @@ __device__ inline void aa_odd_any(S *__restrict__ A, const Geom &g, const Relax<
     }
 }
 
-template <typename S, typename T, bool Forced, int Route>
-__global__ void __launch_bounds__(MaxThreads<T>::value)
-aa_odd_rows_kernel(S *__restrict__ A, Geom g, Relax<T> p, RowGrid R) {
-    int x;
-    uint32_t ri;
-    if (!row_of(R, x, ri) || x >= g.nx) return;
-    int y, z;
-    inner_row(g, ri, y, z);
-    aa_odd_row<S, T, Forced, Route>(A, g, p, x, y, z);
-}
-
-template <typename S, typename T, bool Forced, int Route>
-__global__ void __launch_bounds__(MaxThreads<T>::value)
-aa_odd_rows_face_kernel(S *__restrict__ A, Geom g, Relax<T> p, RowGrid R) {
-    int x;
-    uint32_t ri;
-    if (!row_of(R, x, ri) || x >= g.nx) return;
-    int y, z;
-    face_row(g, R, ri, y, z);
-    aa_odd_any<S, T, Forced, Route>(A, g, p, x, y, z);
-}
-
 // any block shape, row layout: every node with the full rule
 template <typename S, typename T, bool Forced, int Route, bool Odd>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
@@ -287,32 +266,28 @@ aa_any_kernel(S *__restrict__ A, Geom g, Relax<T> p, LaunchGrid L) {
         aa_even_any<S, T, Forced, Route>(A, g, p, x, y, z);
 }
 
-template <typename S, typename T, bool Forced, int Route>
-static hipError_t aa_pair_rows_f(void *A, const Geom &g, const Relax<T> &p, const StepLaunch &c, hipStream_t st) {
-    const int threads = c.bx * c.by;
-    RowGrid R;
-    uint32_t blocks = all_rows(g, threads, c.xcd_remap, R);
+template <typename S, typename T, bool Forced, int Route, bool Far>
+static hipError_t aa_pair_flat(void *A, const Geom &g, const Relax<T> &p, const FlatLaunch &L, int threads,
+                               hipStream_t st) {
     Relax<T> q = p;             // the odd step is the next collision
     q.step = p.step + 1u;
-    hipLaunchKernelGGL((aa_even_rows_kernel<S, T, Forced, Route>), dim3(blocks), dim3(threads), 0, st, (S *)A, g, p, R);
+    hipLaunchKernelGGL((aa_even_flat_kernel<S, T, Forced, Route, Far>), dim3(L.blocks), dim3(threads), 0, st, (S *)A, g,
+                       p, L.grid);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    blocks = inner_rows(g, threads, c.xcd_remap, R);
-    if (blocks > 0) {
-        hipLaunchKernelGGL((aa_odd_rows_kernel<S, T, Forced, Route>), dim3(blocks), dim3(threads), 0, st, (S *)A, g, q,
-                           R);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    blocks = face_rows(g, threads, R);
-    hipLaunchKernelGGL((aa_odd_rows_face_kernel<S, T, Forced, Route>), dim3(blocks), dim3(threads), 0, st, (S *)A, g, q,
-                       R);
+    hipLaunchKernelGGL((aa_odd_flat_kernel<S, T, Forced, Route, Far>), dim3(L.blocks), dim3(threads), 0, st, (S *)A, g,
+                       q, L.grid);
     return hipGetLastError();
 }
 
 template <typename S, typename T, bool Forced, int Route>
 static hipError_t aa_pair_f(void *A, const Geom &g, const Relax<T> &p, const StepLaunch &c, hipStream_t st) {
-    if (g.rows && c.bx % 64 == 0) return aa_pair_rows_f<S, T, Forced, Route>(A, g, p, c, st);
+    if (g.rows) {
+        const int threads = (c.bx * c.by + 63) / 64 * 64;
+        const FlatLaunch F = flat_launch(g, sizeof(S), threads, c.xcd_remap);
+        if (F.near) return aa_pair_flat<S, T, Forced, Route, false>(A, g, p, F, threads, st);
+        if (F.far) return aa_pair_flat<S, T, Forced, Route, true>(A, g, p, F, threads, st);
+    }
     LaunchGrid L;
     L.gx = (g.nx + c.bx - 1) / c.bx;
     L.gy = (g.ny + c.by - 1) / c.by;

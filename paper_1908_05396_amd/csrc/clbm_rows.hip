@@ -34,21 +34,13 @@ namespace clbm {
 template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route, bool Far>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
 stream_collide_rows_flat_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, FlatGrid L) {
-    uint32_t b = blockIdx.x;
-    if (L.remap && b < L.aligned) b = (b & 7u) * (L.aligned >> 3) + (b >> 3);
-    const uint32_t i = b * blockDim.x + threadIdx.x;
-    if (i >= (uint32_t)g.n) return;
-    const uint32_t r = L.by_nx.quotient(i), zr = L.by_ny.quotient(r);
-    const int x = (int)(i - r * (uint32_t)g.nx), y = (int)(r - zr * (uint32_t)g.ny), z = (int)zr;
-    const uint32_t run = (uint32_t)g.nx * (uint32_t)sizeof(S);
-    // Far: offsets count from the layer of the wave's first node
-    const uint32_t r0 = Far ? __builtin_amdgcn_readfirstlane(zr) * (uint32_t)g.ny : 0u;
-    const uint32_t own = (r - r0) * (Q * run) + (uint32_t)x * (uint32_t)sizeof(S);
+    const FlatLane<S, Far> k(g, L);
+    if (k.i >= (uint32_t)g.n) return;
     T d[Q];
-    gather_flat<S, T, LdAux, Far>(A + (int64_t)r0 * g.row, own, g, p, x, y, z, d);
+    gather_flat<S, T, LdAux, Far>(A + k.r0 * g.row, k.own, g, p, k.x, k.y, k.z, d);
     collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    row_store_at<S, T, StAux>(row_rsrc(B + (int64_t)r0 * g.row, 0xFFFFFFFFu), own, run, d, p.sr != 0,
-                              sr_base(i, p.step));
+    row_store_at<S, T, StAux>(row_rsrc(B + k.r0 * g.row, 0xFFFFFFFFu), k.own, (uint32_t)g.nx * (uint32_t)sizeof(S), d,
+                              p.sr != 0, sr_base(k.i, p.step));
 }
 
 template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route>
@@ -72,32 +64,21 @@ template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route>
 static hipError_t launch_rows_k(const S *a, S *b, const Geom &g, const Relax<T> &p, const StepLaunch &c,
                                 hipStream_t st) {
     const int threads = (c.bx * c.by + 63) / 64 * 64;
-    // near: the lattice, a layer and the descriptor's lead fit 32-bit offsets;
-    // far: the layers that a wave's nodes and their sources lie in do
-    const uint64_t row = (uint64_t)Q * sizeof(S) * (uint64_t)g.nx, layer = row * (uint64_t)g.ny;
-    const uint64_t bytes = layer * (uint64_t)g.nz;
-    const bool near = bytes + layer + 2 * row < 0xFFFFFF00ull;
-    const bool far = layer * (uint64_t)(64 / g.nxy + 5) + 2 * row < 0x80000000ull;
+    const FlatLaunch L = flat_launch(g, sizeof(S), threads, c.xcd_remap);
     // Beyond 1 GiB FP32 and FP64 run 0-6% faster with offsets from the wave's
     // own layer (300 x 280 x 290: 733 against 772 us FP32, 1220 against 1299
     // FP64), FP16 between 3% faster and 4% slower.  From 4 GiB FP32 runs 2-6%
     // faster with one wave per run of a row (512^3 3449 against 3524 us; 500^3,
     // whole rows per workgroup, 3569 against 3784), FP64 and FP16 1-14% slower.
-    const bool prefer_far = !std::is_same<S, __half>::value && bytes > ((uint64_t)1 << 30);
-    const bool prefer_rows = std::is_same<S, float>::value && !near && g.nx >= 64;
-    if (!prefer_rows && (near || far)) {
-        FlatGrid L;
-        const uint32_t blocks = (uint32_t)(((int64_t)g.n + threads - 1) / threads);
-        L.by_nx = Divisor::make((uint32_t)g.nx);
-        L.by_ny = Divisor::make((uint32_t)g.ny);
-        L.aligned = blocks & ~7u;
-        L.remap = c.xcd_remap;
-        if (near && !(far && prefer_far))
-            hipLaunchKernelGGL((stream_collide_rows_flat_kernel<S, T, Forced, LdAux, StAux, Route, false>), dim3(blocks),
-                               dim3(threads), 0, st, a, b, g, p, L);
+    const bool prefer_far = !std::is_same<S, __half>::value && (uint64_t)Q * sizeof(S) * (uint64_t)g.n > (1ull << 30);
+    const bool prefer_rows = std::is_same<S, float>::value && !L.near && g.nx >= 64;
+    if (!prefer_rows && (L.near || L.far)) {
+        if (L.near && !(L.far && prefer_far))
+            hipLaunchKernelGGL((stream_collide_rows_flat_kernel<S, T, Forced, LdAux, StAux, Route, false>),
+                               dim3(L.blocks), dim3(threads), 0, st, a, b, g, p, L.grid);
         else
-            hipLaunchKernelGGL((stream_collide_rows_flat_kernel<S, T, Forced, LdAux, StAux, Route, true>), dim3(blocks),
-                               dim3(threads), 0, st, a, b, g, p, L);
+            hipLaunchKernelGGL((stream_collide_rows_flat_kernel<S, T, Forced, LdAux, StAux, Route, true>),
+                               dim3(L.blocks), dim3(threads), 0, st, a, b, g, p, L.grid);
         return hipGetLastError();
     }
     RowGrid R;

@@ -25,7 +25,6 @@ struct RowGrid {
     uint32_t rows;          // rows handled by the launch
     uint32_t aligned;       // largest multiple of 8 <= number of workgroups
     int32_t remap;          // XCD-contiguous workgroup order
-    int32_t zf, yf;         // face rows: z faces (1 or 2) and y faces (1 or 2)
 };
 
 // Column of the lane and row index of the wave.
@@ -58,50 +57,15 @@ struct FlatGrid {
     int32_t remap;          // XCD-contiguous workgroup order
 };
 
-// inner rows: y in [1, ny - 2], z in [1, nz - 2]
-__device__ inline void inner_row(const Geom &g, uint32_t ri, int &y, int &z) {
-    const uint32_t w = (uint32_t)g.ny - 2u;
-    y = 1 + (int)(ri % w);
-    z = 1 + (int)(ri / w);
-}
-
-// face rows: every row of the z faces, then the y-face rows of the inner z layers
-__device__ inline void face_row(const Geom &g, const RowGrid &R, uint32_t ri, int &y, int &z) {
-    const uint32_t nzr = (uint32_t)R.zf * (uint32_t)g.ny;
-    if (ri < nzr) {
-        y = (int)(ri % (uint32_t)g.ny);
-        z = ri < (uint32_t)g.ny ? 0 : g.nz - 1;
-    } else {
-        const uint32_t k = ri - nzr;
-        z = 1 + (int)(k / (uint32_t)R.yf);
-        y = (k % (uint32_t)R.yf) == 0 ? 0 : g.ny - 1;
-    }
-}
-
-// Workgroups of `threads` threads (a multiple of 64) over `rows` rows.
-inline uint32_t row_blocks(const Geom &g, uint32_t rows, int threads, int remap, RowGrid &R) {
+// Workgroups of `threads` threads (a multiple of 64) over every row of the lattice.
+inline uint32_t all_rows(const Geom &g, int threads, int remap, RowGrid &R) {
     R.gx = ((uint32_t)g.nx + 63u) / 64u;
-    R.rows = rows;
-    R.zf = g.nz > 1 ? 2 : 1;
-    R.yf = g.ny > 1 ? 2 : 1;
+    R.rows = (uint32_t)g.ny * (uint32_t)g.nz;
     R.remap = remap;
     const uint32_t waves = (uint32_t)threads / 64u;
-    const uint32_t blocks = (uint32_t)(((uint64_t)R.gx * rows + waves - 1) / waves);
+    const uint32_t blocks = (uint32_t)(((uint64_t)R.gx * R.rows + waves - 1) / waves);
     R.aligned = blocks & ~7u;
     return blocks;
-}
-
-// One launch over every row of the lattice, or the inner and the face rows
-// apart (the inner rows may be none: ny or nz below 3).
-inline uint32_t all_rows(const Geom &g, int threads, int remap, RowGrid &R) {
-    return row_blocks(g, (uint32_t)g.ny * (uint32_t)g.nz, threads, remap, R);
-}
-inline uint32_t inner_rows(const Geom &g, int threads, int remap, RowGrid &R) {
-    return row_blocks(g, (g.ny > 2 && g.nz > 2) ? (uint32_t)(g.ny - 2) * (uint32_t)(g.nz - 2) : 0u, threads, remap, R);
-}
-inline uint32_t face_rows(const Geom &g, int threads, RowGrid &R) {
-    const uint32_t zf = g.nz > 1 ? 2 : 1, yf = g.ny > 1 ? 2 : 1;
-    return row_blocks(g, zf * (uint32_t)g.ny + (g.nz > 2 ? (uint32_t)(g.nz - 2) * yf : 0u), threads, 0, R);
 }
 
 // Row kernels group the x-face bounce-back loads of a wave (row_gather's
@@ -272,68 +236,148 @@ __device__ inline void row_store(S *__restrict__ B, const Geom &g, int x, int y,
     row_store_at<S, T, StAux>(out, (uint32_t)x * es, run, d, sr, seed_base);
 }
 
-// Pull gather of 64 consecutive nodes with the full wall logic (Eq. cascaded
-// streaming with the rules of Sec. 4) on every lane: periodic wrap, half-way
-// bounce-back, moving lid.  Which value a direction reads - the source's, or
-// the node's own opposite population beyond a wall - is a select on its
-// address, so the 19 loads go out together and the wave waits for memory once;
-// the lid terms are added afterwards, in waves that touch the lid.
+// ---------------------------------------------------------------------------
+// Waves of 64 consecutive nodes (x fastest, across rows and layers): each lane
+// addresses its sources with the full wall logic (Eq. cascaded streaming with
+// the rules of Sec. 4): periodic wrap, half-way bounce-back, moving lid.
+// Which value a direction reads - the source's, or the node's own beyond a
+// wall - is a select on its address, so the 19 loads go out together and the
+// wave waits for memory once; the lid terms are added afterwards, in waves that
+// touch the lid.
 //
-// `own` is the byte offset from A of the node's own row group plus its x, and
-// every source lies within 32 bits of it: loads go through one descriptor
-// that starts K = layer + row + one value before A (no access falls before A),
-// which keeps the lane offsets positive.  Far: the lattice itself is larger;
-// lanes that pull across a periodic z face then address in 64 bits.
+// `own` is the byte offset of the node's own row group plus its x from the
+// base that the loads use, and every source lies within 32 bits of it: loads
+// go through one descriptor that starts K = layer + row + one value before that
+// base (no access falls before it), which keeps the lane offsets positive.
+// Far: the lattice itself is larger; the base is the layer of the wave's first
+// node, and lanes that pull across a periodic z face address in 64 bits.
 //
 // Waves without a face node could use one lane offset and 19 scalar ones.
 // Their loads then issue back to back, which the memory serves worse than
 // loads a few instructions apart: 200 x 190 x 220 FP32 304 us per step with
 // that path against 250 without, 256^3 FP16 233 against 227; not kept.
-template <typename S, typename T, int LdAux, bool Far>
-__device__ __forceinline__ void gather_flat(const S *__restrict__ A, uint32_t own, const Geom &g, const Relax<T> &p, int x,
-                                   int y, int z, T (&d)[Q]) {
-    constexpr uint32_t es = sizeof(S);
-    const uint32_t run = (uint32_t)g.nx * es, row = Q * run, layer = row * (uint32_t)g.ny, K = layer + row + es;
-    const bool lo[3] = {x == 0, y == 0, z == 0};
-    const bool hi[3] = {x == g.nx - 1, y == g.ny - 1, z == g.nz - 1};
-    const bool per[3] = {g.px != 0, g.py != 0, g.pz != 0};
-    // per axis, index c + 1 for c = -1, 0, +1: byte distance to the (wrapped)
-    // source (Far: lanes wrapping in z read their own layer here and are redone below)
-    const uint32_t wrap = Far ? layer : layer * (uint32_t)g.nz;
-    const uint32_t dx[3] = {hi[0] ? es - run : es, 0u, lo[0] ? run - es : 0u - es};
-    const uint32_t dy[3] = {hi[1] ? row - layer : row, 0u, lo[1] ? layer - row : 0u - row};
-    const uint32_t dz[3] = {hi[2] ? layer - wrap : layer, 0u, lo[2] ? wrap - layer : 0u - layer};
-    auto ghost = [&](int axis, int c) { return c != 0 && !per[axis] && (c == 1 ? lo[axis] : hi[axis]); };
-    const __amdgpu_buffer_rsrc_t rsrc = row_rsrc((const char *)A - K, 0xFFFFFFFFu);
-    const uint32_t self = own + K;
-#pragma unroll
-    for (int a = 0; a < Q; ++a) {
-        const bool wall = ghost(0, cx(a)) | ghost(1, cy(a)) | ghost(2, cz(a));
-        const uint32_t src = self + dx[cx(a) + 1] + dy[cy(a) + 1] + dz[cz(a) + 1];
-        d[a] = (T)RawBits<S>::template load<LdAux>(rsrc, wall ? self + (uint32_t)(opp(a) - a) * run : src,
-                                                   (uint32_t)a * run);
+// ---------------------------------------------------------------------------
+template <typename S, bool Far> struct FlatNode {
+    uint32_t run, layer, self;          // bytes; self: own + K
+    uint32_t xm, xp, ym, yp, zm, zp;    // byte distance to the (wrapped) source for c = -1 (m) and +1 (p)
+    bool lo[3], hi[3], per[3];          // on the low and high face of an axis; periodic
+    int lid_mask;
+
+    __device__ __forceinline__ FlatNode(const Geom &g, uint32_t own, int x, int y, int z) {
+        constexpr uint32_t es = sizeof(S);
+        run = (uint32_t)g.nx * es;
+        const uint32_t row = Q * run;
+        layer = row * (uint32_t)g.ny;
+        self = own + lead();
+        lo[0] = x == 0; lo[1] = y == 0; lo[2] = z == 0;
+        hi[0] = x == g.nx - 1; hi[1] = y == g.ny - 1; hi[2] = z == g.nz - 1;
+        per[0] = g.px != 0; per[1] = g.py != 0; per[2] = g.pz != 0;
+        lid_mask = g.lid_mask;
+        // (Far: lanes wrapping in z point at their own layer)
+        const uint32_t wrap = Far ? layer : layer * (uint32_t)g.nz;
+        xm = hi[0] ? es - run : es;
+        xp = lo[0] ? run - es : 0u - es;
+        ym = hi[1] ? row - layer : row;
+        yp = lo[1] ? layer - row : 0u - row;
+        zm = hi[2] ? layer - wrap : layer;
+        zp = lo[2] ? wrap - layer : 0u - layer;
     }
-    const int m = g.lid_mask;
-    auto lid = [&](int axis, int c) {
-        return c != 0 && (c == 1 ? ((m >> (2 * axis)) & 1) && lo[axis] : ((m >> (2 * axis + 1)) & 1) && hi[axis]);
-    };
-    const bool any = lid(0, 1) | lid(0, -1) | lid(1, 1) | lid(1, -1) | lid(2, 1) | lid(2, -1);
-    if (__builtin_amdgcn_ballot_w64(any) != 0) {
+    __device__ uint32_t lead() const { return layer + Q * run + (uint32_t)sizeof(S); }
+    __device__ __amdgpu_buffer_rsrc_t rsrc(const S *base) const { 
+        // (Far: offsets stay below 2^31, so that 0x80000000 lies outside whether or not scalar offsets count)
+        return row_rsrc((const char *)base - lead(), Far ? 0x80000000u : 0xFFFFFFFFu);
+    }
+    __device__ bool ghost(int axis, int c) const { return c != 0 && !per[axis] && (c == 1 ? lo[axis] : hi[axis]); }
+    __device__ bool wall(int a) const { return ghost(0, cx(a)) | ghost(1, cy(a)) | ghost(2, cz(a)); }
+    // lane offset of the source of direction a (run 0 of its row group)
+    __device__ uint32_t source(int a) const { return self + dxy(a) + (cz(a) == 0 ? 0u : cz(a) == 1 ? zp : zm); }
+    __device__ uint32_t dxy(int a) const {
+        return (cx(a) == 0 ? 0u : cx(a) == 1 ? xp : xm) + (cy(a) == 0 ? 0u : cy(a) == 1 ? yp : ym);
+    }
+    // the source of direction a is a ghost in the lid plane (edges and corners of it included)
+    __device__ bool lid(int axis, int c) const {
+        return c != 0 && (c == 1 ? ((lid_mask >> (2 * axis)) & 1) && lo[axis]
+                                 : ((lid_mask >> (2 * axis + 1)) & 1) && hi[axis]);
+    }
+    __device__ bool lid(int a) const { return lid(0, cx(a)) | lid(1, cy(a)) | lid(2, cz(a)); }
+    __device__ bool wave_touches_lid() const {
+        const bool any = lid(0, 1) | lid(0, -1) | lid(1, 1) | lid(1, -1) | lid(2, 1) | lid(2, -1);
+        return __builtin_amdgcn_ballot_w64(any) != 0;
+    }
+    // Far: direction a's source lies across a periodic z face, at this byte
+    // distance from the node's own row group
+    __device__ bool wraps(int a) const { return Far && per[2] && cz(a) != 0 && (cz(a) == 1 ? lo[2] : hi[2]) && !wall(a); }
+    __device__ int64_t wrapped(const Geom &g, int a) const {
+        return (int64_t)(int32_t)dxy(a) + cz(a) * (int64_t)(g.nz - 1) * (int64_t)layer;
+    }
+};
+
+template <typename S, typename T, int LdAux, bool Far>
+__device__ __forceinline__ void gather_flat(const S *__restrict__ A, uint32_t own, const Geom &g, const Relax<T> &p,
+                                            int x, int y, int z, T (&d)[Q]) {
+    const FlatNode<S, Far> f(g, own, x, y, z);
+    const __amdgpu_buffer_rsrc_t rsrc = f.rsrc(A);
 #pragma unroll
-        for (int a = 1; a < Q; ++a)
-            d[a] = wall_value<T>(d[a], p, a, lid(0, cx(a)) | lid(1, cy(a)) | lid(2, cz(a)));
+    for (int a = 0; a < Q; ++a)
+        d[a] = (T)RawBits<S>::template load<LdAux>(
+            rsrc, f.wall(a) ? f.self + (uint32_t)(opp(a) - a) * f.run : f.source(a), (uint32_t)a * f.run);
+    if (f.wave_touches_lid()) {
+#pragma unroll
+        for (int a = 1; a < Q; ++a) d[a] = wall_value<T>(d[a], p, a, f.lid(a));
     }
     if constexpr (Far) {
-        if (per[2] && (lo[2] || hi[2])) {
+        if (g.pz && (f.lo[2] || f.hi[2])) {
 #pragma unroll
-            for (int a = 1; a < Q; ++a) {
-                if (cz(a) == 0 || !(cz(a) == 1 ? lo[2] : hi[2]) || ghost(0, cx(a)) || ghost(1, cy(a))) continue;
-                const int64_t to = (int64_t)(int32_t)(dx[cx(a) + 1] + dy[cy(a) + 1]) + (int64_t)a * run +
-                                   cz(a) * (int64_t)(g.nz - 1) * (int64_t)layer;
-                d[a] = (T)Conv<S, T>::load(*(const S *)((const char *)A + own + to));
-            }
+            for (int a = 1; a < Q; ++a)
+                if (cz(a) != 0 && f.wraps(a))
+                    d[a] = (T)Conv<S, T>::load(
+                        *(const S *)((const char *)A + own + f.wrapped(g, a) + (int64_t)a * f.run));
         }
     }
 }
+
+// Workgroups over the nodes of a lattice, and whether 32-bit offsets reach
+// the whole of it (near) or the layers of a wave's nodes and their sources
+// (far).
+struct FlatLaunch {
+    FlatGrid grid;
+    uint32_t blocks;
+    bool near, far;
+};
+
+inline FlatLaunch flat_launch(const Geom &g, uint64_t value_bytes, int threads, int remap) {
+    FlatLaunch L;
+    const uint64_t row = (uint64_t)Q * value_bytes * (uint64_t)g.nx, layer = row * (uint64_t)g.ny;
+    L.near = layer * (uint64_t)g.nz + layer + 2 * row < 0xFFFFFF00ull;
+    L.far = layer * (uint64_t)(64 / g.nxy + 5) + 2 * row < 0x80000000ull;
+    L.blocks = (uint32_t)(((int64_t)g.n + threads - 1) / threads);
+    L.grid.by_nx = Divisor::make((uint32_t)g.nx);
+    L.grid.by_ny = Divisor::make((uint32_t)g.ny);
+    L.grid.aligned = L.blocks & ~7u;
+    L.grid.remap = remap;
+    return L;
+}
+
+// The lane's node of a flat launch: its coordinates, the first row of the
+// base that 32-bit offsets count from (0, or Far: of the layer of the wave's
+// first node) and its own offset from there.
+template <typename S, bool Far> struct FlatLane {
+    uint32_t i, own;
+    int64_t r0;
+    int x, y, z;
+    __device__ __forceinline__ FlatLane(const Geom &g, const FlatGrid &L) {
+        uint32_t b = blockIdx.x;
+        if (L.remap && b < L.aligned) b = (b & 7u) * (L.aligned >> 3) + (b >> 3);
+        i = b * blockDim.x + threadIdx.x;
+        if (i >= (uint32_t)g.n) return;
+        const uint32_t r = L.by_nx.quotient(i), zr = L.by_ny.quotient(r);
+        x = (int)(i - r * (uint32_t)g.nx);
+        y = (int)(r - zr * (uint32_t)g.ny);
+        z = (int)zr;
+        const uint32_t first = Far ? __builtin_amdgcn_readfirstlane(zr) * (uint32_t)g.ny : 0u;
+        r0 = first;
+        own = (r - first) * (Q * (uint32_t)g.nx * (uint32_t)sizeof(S)) + (uint32_t)x * (uint32_t)sizeof(S);
+    }
+};
 
 }  // namespace clbm
