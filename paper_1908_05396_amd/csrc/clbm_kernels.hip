@@ -12,7 +12,7 @@
 //   reduce_final          fixed-order sum of the partials
 #include <mutex>
 
-#include "clbm_internal.hpp"
+#include "clbm_rows.hpp"
 
 namespace clbm {
 
@@ -65,8 +65,9 @@ stream_collide_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<
 // (Sec. 4.1) returns the node's own post-collision population opposite to a,
 // plus the moving-wall term (Sec. 4.3) for a moving solid node or a ghost in
 // the lid plane.  Solid nodes are not part of the fluid and hold the rest
-// state (zero deviations).  One thread per node in either layout; plain
-// loads (the flags of the 18 neighbours come from cache).
+// state (zero deviations).  This kernel takes one thread per node in either
+// layout, direction by direction (the planes layout, and layers beyond the
+// reach of 32-bit offsets).
 // ---------------------------------------------------------------------------
 template <typename S, typename T>
 __device__ inline T pull_flagged(const S *__restrict__ A, const uint8_t *__restrict__ flags, const Geom &g,
@@ -105,6 +106,63 @@ stream_collide_flags_kernel(const S *__restrict__ A, S *__restrict__ B, const ui
     }
 #pragma unroll
     for (int a = 0; a < Q; ++a) B[elem(g, a, x, y, z)] = Conv<S, T>::store(d[a]);
+}
+
+// The same step on the row layout, in waves of 64 consecutive nodes by address
+// selects (FlatNode): the 18 source flags first, all together, then the 19
+// populations, all together - two waits for memory instead of one per
+// direction.  150 x 100 x 90 FP32: 33.7 us per step against 57.5.
+template <typename S, typename T, bool Forced, int Route, bool Far>
+__global__ void __launch_bounds__(256)
+stream_collide_flags_flat_kernel(const S *__restrict__ A, S *__restrict__ B, const uint8_t *__restrict__ flags, Geom g,
+                                 Relax<T> p, FlatGrid L) {
+    const FlatLane<S, Far> k(g, L);
+    if (k.i >= (uint32_t)g.n) return;
+    const FlatNode<S, Far> f(g, k.own, k.x, k.y, k.z);
+    const S *Aw = A + k.r0 * g.row;
+    // flags: offsets in nodes, from a layer, a row and a node before the array
+    const uint32_t lead = (uint32_t)g.nxy + (uint32_t)g.nx + 1u, self = k.i + lead;
+    const __amdgpu_buffer_rsrc_t fr = row_rsrc(flags - lead, (uint32_t)g.n + lead);
+    const uint32_t xm = f.hi[0] ? 1u - (uint32_t)g.nx : 1u, xp = f.lo[0] ? (uint32_t)g.nx - 1u : 0u - 1u;
+    const uint32_t ym = f.hi[1] ? (uint32_t)(g.nx - g.nxy) : (uint32_t)g.nx, yp = f.lo[1] ? (uint32_t)(g.nxy - g.nx) : 0u - (uint32_t)g.nx;
+    const uint32_t zm = f.hi[2] ? (uint32_t)(g.nxy - g.n) : (uint32_t)g.nxy, zp = f.lo[2] ? (uint32_t)(g.n - g.nxy) : 0u - (uint32_t)g.nxy;
+    uint8_t fl[Q];
+#pragma unroll
+    for (int a = 0; a < Q; ++a) {
+        const uint32_t src = self + (cx(a) == 0 ? 0u : cx(a) == 1 ? xp : xm) + (cy(a) == 0 ? 0u : cy(a) == 1 ? yp : ym) +
+                             (cz(a) == 0 ? 0u : cz(a) == 1 ? zp : zm);
+        fl[a] = __builtin_amdgcn_raw_buffer_load_b8(fr, (int)(f.wall(a) ? self : src), 0, 0);
+    }
+    T d[Q];
+#pragma unroll
+    for (int a = 0; a < Q; ++a) d[a] = T(0);
+    if (fl[0] == 0) {
+        const __amdgpu_buffer_rsrc_t rsrc = f.rsrc(Aw);
+        bool moving = false;
+#pragma unroll
+        for (int a = 0; a < Q; ++a) {
+            // (beyond a wall of the box fl[a] is the node's own flag, 0)
+            const bool wall = a != 0 && (f.wall(a) || fl[a] != 0);
+            d[a] = (T)RawBits<S>::template load<0>(rsrc, wall ? f.self + (uint32_t)(opp(a) - a) * f.run : f.source(a),
+                                                   (uint32_t)a * f.run);
+            moving = moving || fl[a] == 2 || f.lid(a);
+        }
+        if (__builtin_amdgcn_ballot_w64(moving) != 0) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a) d[a] = wall_value<T>(d[a], p, a, f.lid(a) || fl[a] == 2);
+        }
+        if constexpr (Far) {
+            if (g.pz && (f.lo[2] || f.hi[2])) {
+#pragma unroll
+                for (int a = 1; a < Q; ++a)
+                    if (cz(a) != 0 && f.wraps(a) && fl[a] == 0)
+                        d[a] = (T)Conv<S, T>::load(
+                            *(const S *)((const char *)Aw + k.own + f.wrapped(g, a) + (int64_t)a * f.run));
+            }
+        }
+        collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
+    }
+    row_store_at<S, T, 0>(row_rsrc(B + k.r0 * g.row, 0xFFFFFFFFu), k.own, f.run, d, p.sr != 0, sr_base(k.i, p.step));
 }
 
 // Any flag other than fluid (0), wall (1) or moving wall (2) sets *bad.
@@ -529,6 +587,18 @@ hipError_t launch_init(int storage, const double *f0, void *B, const uint8_t *fl
 template <typename S, typename T, bool Forced, int Route>
 static void launch_flags_k(const void *A, void *B, const uint8_t *flags, const Geom &g, const Relax<T> &p,
                            hipStream_t st) {
+    if (g.rows) {
+        const FlatLaunch L = flat_launch(g, sizeof(S), 256, 1);
+        if (L.near || L.far) {
+            if (L.near)
+                hipLaunchKernelGGL((stream_collide_flags_flat_kernel<S, T, Forced, Route, false>), dim3(L.blocks),
+                                   dim3(256), 0, st, (const S *)A, (S *)B, flags, g, p, L.grid);
+            else
+                hipLaunchKernelGGL((stream_collide_flags_flat_kernel<S, T, Forced, Route, true>), dim3(L.blocks),
+                                   dim3(256), 0, st, (const S *)A, (S *)B, flags, g, p, L.grid);
+            return;
+        }
+    }
     hipLaunchKernelGGL((stream_collide_flags_kernel<S, T, Forced, Route>), dim3((unsigned)((g.n + 255) / 256)),
                        dim3(256), 0, st, (const S *)A, (S *)B, flags, g, p);
 }
