@@ -93,6 +93,95 @@ template <typename S, typename T> __device__ inline T round_trip(T v) {
 
 }  // namespace
 
+// Row layout: the first-step inputs of a wave's row in one plane, issued as 19
+// loads (`issue`) and completed later (`finish`), so that they are in flight
+// over the barrier and the second step.  The wave's row (y) is uniform and a
+// plane's height uniform over the workgroup, so a direction's source is one of
+// three lane offsets (by e_x) plus a scalar offset.  A ghost beyond a y or z wall
+// is a scalar select of the node's own run of the opposite direction; the lanes
+// of a non-periodic x face select it on their own offset.  Both offsets carry a
+// lead of two layers and more (the descriptor starts that far before the
+// node's row group; nothing before the state is accessed), so that neither
+// goes negative; lanes without a column take an offset outside the range.
+template <typename S, typename T> struct RowInputs {
+    uint32_t run, row, layer;
+    uint32_t o0, op, om;        // lane offsets for e_x = 0, +1, -1
+    bool xlo, xhi;              // lane on a non-periodic x face
+
+    __device__ __forceinline__ RowInputs(const Geom &g, int x, bool col) {
+        constexpr uint32_t es = sizeof(S), outside = 0x80000000u;
+        run = __builtin_amdgcn_readfirstlane((uint32_t)g.nx * es);
+        row = Q * run;
+        layer = row * (uint32_t)g.ny;
+        const bool lo = x == 0, hi = x == g.nx - 1;
+        const uint32_t o = lane_lead() + (uint32_t)x * es;
+        o0 = col ? o : outside;
+        op = col ? (lo ? o + run - es : o - es) : outside;
+        om = col ? (hi ? o - run + es : o + es) : outside;
+        xlo = lo && !g.px && col;
+        xhi = hi && !g.px && col;
+    }
+    __device__ uint32_t lane_lead() const { return 2 * layer + row; }
+    __device__ uint32_t run_lead() const { return 2 * layer; }
+
+    // The scalar offsets are rebuilt on every plane instead of being kept (and
+    // spilled) over the loop: the empty asm hides the loop invariance of what
+    // they derive from.
+    template <int Aux>
+    __device__ __forceinline__ void issue(const S *A, const Geom &g, int y, int z, T (&d)[Q]) const {
+        uint32_t run = __builtin_amdgcn_readfirstlane(this->run);
+        y = __builtin_amdgcn_readfirstlane(y);
+        asm volatile("" : "+s"(run), "+s"(y));
+        const int ylo = y == 0, yhi = y == g.ny - 1;
+        const uint32_t row = Q * run, layer = row * (uint32_t)g.ny;
+        auto lane_lead = [&] { return 2 * layer + row; };
+        auto run_lead = [&] { return 2 * layer; };
+        // byte distance to the source row and layer for c = -1 (m) and +1 (p), and whether it is a ghost
+        const uint32_t ym = yhi ? row - layer : row, yp = ylo ? layer - row : 0u - row;
+        const int gym = yhi & (g.py ^ 1), gyp = ylo & (g.py ^ 1);
+        const int gzm = (z == g.nz - 1) & (g.pz ^ 1), gzp = (z == 0) & (g.pz ^ 1);
+        const __amdgpu_buffer_rsrc_t r = row_rsrc(
+            (const char *)(A + ((int64_t)z * g.ny + y) * g.row) - (lane_lead() + run_lead()), 0x80000000u);
+        const bool xface = __builtin_amdgcn_ballot_w64(xlo || xhi) != 0;
+#pragma unroll
+        for (int a = 0; a < Q; ++a) {
+            const int wall = (cy(a) == 0 ? 0 : cy(a) == 1 ? gyp : gym) | (cz(a) == 0 ? 0 : cz(a) == 1 ? gzp : gzm);
+            const uint32_t dist = (cy(a) == 0 ? 0u : cy(a) == 1 ? yp : ym) +
+                                  (cz(a) == 0 ? 0u : cz(a) == 1 ? 0u - layer : layer);
+            const uint32_t so = run_lead() + (wall ? (uint32_t)opp(a) * run : (uint32_t)a * run + dist);
+            uint32_t vo = o0;
+            if (cx(a) != 0) {
+                vo = wall ? o0 : (cx(a) == 1 ? op : om);
+                if (xface) vo = (cx(a) == 1 ? xlo : xhi) ? o0 + (run_lead() + (uint32_t)opp(a) * run - so) : vo;
+            }
+            d[a] = (T)RawBits<S>::template load<Aux>(r, vo, so);
+        }
+    }
+
+    // moving wall: ghosts in the lid plane (edges and corners of it included)
+    __device__ __forceinline__ void finish(const Geom &g, const Relax<T> &p, int y, int z, T (&d)[Q]) const {
+        int m = g.lid_mask;
+        if (m == 0) return;
+        y = __builtin_amdgcn_readfirstlane(y);
+        asm volatile("" : "+s"(m), "+s"(y));
+        const int ylo = y == 0, yhi = y == g.ny - 1;
+        auto lid = [&](auto crosses) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a)
+                if (crosses(a)) d[a] = wall_value<T>(d[a], p, a, true);
+        };
+        if ((m & 4) && ylo) lid([](int a) { return cy(a) == 1; });
+        if ((m & 8) && yhi) lid([](int a) { return cy(a) == -1; });
+        if ((m & 16) && z == 0) lid([](int a) { return cz(a) == 1; });
+        if ((m & 32) && z == g.nz - 1) lid([](int a) { return cz(a) == -1; });
+        if (m & 3) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a)
+                if (cx(a) != 0) d[a] = wall_value<T>(d[a], p, a, cx(a) == 1 ? (m & 1) && xlo : (m & 2) && xhi);
+        }
+    }
+};
+
 struct FusedGrid {
     uint32_t gx, gy, gz;    // patches along x and y, z chunks
     int32_t cz;             // output planes per z chunk
@@ -101,8 +190,9 @@ struct FusedGrid {
 };
 
 // StAux: cache hint of the population stores (0 plain, 2 non-temporal);
-// Rows: row layout (else planes)
-template <typename S, typename T, bool Forced, int Route, int ROWS, bool PF, int StAux, bool Rows>
+// Rows: row layout (else planes); Pipe: its loads a plane ahead (no periodic z
+// axis, eight layers within 2^31 bytes)
+template <typename S, typename T, bool Forced, int Route, int ROWS, bool PF, int StAux, bool Rows, bool Pipe>
 __global__ void __launch_bounds__(kLanes * ROWS)
 stream_collide2_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, FusedGrid L) {
     static_assert(!(Rows && PF), "the direct-to-LDS prefetch reads the planes layout");
@@ -131,10 +221,19 @@ stream_collide2_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax
     bool col = gx <= min(g.nx, tx * kOut + kOut) && gy <= min(g.ny, ty * (ROWS - 2) + ROWS - 2);
     if (wx < 0 || wx >= g.nx) { if (g.px) wx = wx < 0 ? wx + g.nx : wx - g.nx; else col = false; }
     if (wy < 0 || wy >= g.ny) { if (g.py) wy = wy < 0 ? wy + g.ny : wy - g.ny; else col = false; }
+    const bool row_ok = __builtin_amdgcn_ballot_w64(col) != 0;     // the wave's row exists
 
     T r0c[3], r0n[3];              // e_z = 0,  e_y = 0 of I(z), I(z + 1)
     T rpp[3], rpc[3], rpn[3];      // e_z = +1, e_y = 0 of I(z - 1), I(z), I(z + 1)
     T rmc[3], rmn[3];              // e_z = -1, e_y = 0 of I(z), I(z + 1)
+
+    // Row layout: the 19 loads of plane m into registers, issued a plane ahead.
+    const RowInputs<S, T> in(g, wx, col);
+    auto issue = [&](int m, T (&d)[Q]) {
+        if constexpr (Pipe) {
+            if (row_ok && m >= 0 && m < g.nz) in.template issue<0>(A, g, wy, m, d);
+        }
+    };
 
     // Issue the interior pull loads of plane m straight into this wave's row
     // of sh.in (no registers held while they are in flight).
@@ -160,20 +259,23 @@ stream_collide2_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax
     };
 
     // I(m) into LDS ring slots (index jm = m - z0 + 1) and the given registers
-    auto first_step = [&](int m, int jm, T (&o0)[3], T (&op)[3], T (&om)[3]) {
+    auto first_step = [&](int m, int jm, T (&d)[Q], T (&o0)[3], T (&op)[3], T (&om)[3]) {
         // The buffer descriptors of the 19 planes are rebuilt from the base
         // pointer on every plane instead of being kept (and spilled) across
         // the loop: the empty asm hides the pointer's loop invariance.
         const S *Am = A;
         asm volatile("" : "+s"(Am));
         int wz = m;
-        bool v = col;
+        bool v = Pipe ? row_ok : col;     // (Pipe: lanes without a column hold zeros)
         if (wz < 0 || wz >= g.nz) { if (g.pz) wz = wz < 0 ? wz + g.nz : wz - g.nz; else v = false; }
-        T d[Q];
-        if constexpr (PF) __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // this wave's prefetch has landed
+        if constexpr (!Rows) {
+            if constexpr (PF) __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // this wave's prefetch has landed
+        }
         if (v) {
             const uint32_t self = (uint32_t)wx + (uint32_t)g.nx * (uint32_t)wy + (uint32_t)g.nxy * (uint32_t)wz;
-            if constexpr (Rows) {
+            if constexpr (Pipe) {
+                in.finish(g, p, wy, wz, d);
+            } else if constexpr (Rows) {
                 // the wave's row (wy, wz) is uniform: off the y and z faces, or on one
                 if (wy >= 1 && wy <= g.ny - 2 && wz >= 1 && wz <= g.nz - 2)
                     row_gather<S, T, 0, false, XGroupRows<S>::value>(A, g, p, wx, wy, wz, d);
@@ -265,15 +367,26 @@ stream_collide2_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax
     };
 
     // plane m = z0 - 1 .. z1: first step of I(m), then the output plane m - 1
+    T d[Q];
+#pragma unroll
+    for (int a = 0; a < Q; ++a) d[a] = T(0);
     prefetch(z0 - 1);
+    issue(z0 - 1, d);
     for (int m = z0 - 1; m <= z1; ++m) {
-        first_step(m, m - z0 + 1, r0n, rpn, rmn);
-        if (m < z1) prefetch(m + 1);
+        first_step(m, m - z0 + 1, d, r0n, rpn, rmn);
+        if (m < z1) {
+            prefetch(m + 1);
+            issue(m + 1, d);
+        }
         if constexpr (PF) {
             // only the LDS ring writes must be visible to the other waves; the
             // prefetch stays in flight across the barrier
             __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
             __builtin_amdgcn_s_barrier();
+        } else if constexpr (Pipe) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         } else {
             __syncthreads();
         }
@@ -300,12 +413,12 @@ static hipError_t launch2_f(const void *A, void *B, const Geom &g, const Relax<T
     if (nb == 0 || nb > 0x7fffffffull) return hipErrorInvalidValue;
     L.aligned = (uint32_t)nb & ~7u;
     L.remap = c.xcd_remap;
-    if (c.nt_stores)
-        hipLaunchKernelGGL((stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 2, Rows>), dim3((uint32_t)nb),
-                           dim3(kLanes * ROWS), 0, st, (const S *)A, (S *)B, g, p, L);
-    else
-        hipLaunchKernelGGL((stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 0, Rows>), dim3((uint32_t)nb),
-                           dim3(kLanes * ROWS), 0, st, (const S *)A, (S *)B, g, p, L);
+    const bool pipe = Rows && !g.pz && (uint64_t)Q * sizeof(S) * (uint64_t)g.nxy * 8u < 0x80000000ull;
+    auto k = pipe ? (c.nt_stores ? stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 2, Rows, Rows>
+                                 : stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 0, Rows, Rows>)
+                  : (c.nt_stores ? stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 2, Rows, false>
+                                 : stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 0, Rows, false>);
+    hipLaunchKernelGGL(k, dim3((uint32_t)nb), dim3(kLanes * ROWS), 0, st, (const S *)A, (S *)B, g, p, L);
     return hipGetLastError();
 }
 
