@@ -124,9 +124,10 @@ BEST_FORM = {"f32": "two", "f16": "one", "f64": "one"}
 
 
 def launch_of(form, storage, spec):
-    """Launch dict of a form ("one": library default, "two": TWO_STEP)."""
+    """Launch dict of a form ("one": library default, "two": TWO_STEP).  FP32 names its one step per launch, since
+    the library runs pairs of steps together by default there."""
     if form != "two":
-        return None
+        return {"fuse_steps": 1} if storage == "f32" else None
     c = dict(TWO_STEP[storage])
     c["fuse_planes"] = min(spec.nz, c["fuse_planes"])
     return c

@@ -230,7 +230,8 @@ clbm_status clbm_init_populations(clbm_lattice *h, const double *f0, int on_devi
 /* Advance nsteps time steps (>= 0; Sec. 3: collision, Eq. cascaded
  * collision with the local relaxation rate of Sec. 3.2, then streaming,
  * Eq. cascaded streaming, with the wall rules of Sec. 4): one fused pull
- * stream-collide launch per step (two steps per launch with fuse_steps = 2;
+ * stream-collide launch per step (two steps per launch with fuse_steps = 2, or
+ * by the library's choice while no launch configuration has been set;
  * in the in-place form one launch per step and nsteps even).  Asynchronous;
  * no host synchronization, no allocation, no NaN check (clbm_reduce does
  * that).  EINVAL for nsteps < 0, ESTATE before an init call. */
@@ -310,6 +311,11 @@ typedef struct {
     int32_t reserved;    /* must be 0 */
 } clbm_launch;
 
+/* Until a configuration is set (clbm_set_launch, clbm_set_block,
+ * clbm_autotune), clbm_step may run pairs of steps of FP32 row-layout lattices
+ * as two-step launches of its own choice where these run faster;
+ * clbm_get_launch reports the one-step configuration that it uses otherwise
+ * (and for an odd remainder). */
 clbm_status clbm_set_launch(clbm_lattice *h, const clbm_launch *cfg);
 clbm_status clbm_get_launch(clbm_lattice *h, clbm_launch *cfg);
 

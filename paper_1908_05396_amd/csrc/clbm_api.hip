@@ -26,6 +26,8 @@ struct clbm_lattice {
     bool initialized;
     int64_t steps_done;
     StepLaunch launch;
+    bool pair_steps;        // until a launch is set: pairs of steps run as two-step launches of shape `pair`
+    StepLaunch pair;
     // reduction scratch (library-owned)
     double *partials;
     double *result;
@@ -35,12 +37,6 @@ struct clbm_lattice {
     bool have_snapshot;
 };
 
-// Default launch form (measured on the 512^3 cavity, MI355X, in the developed
-// flow): one step per launch for every storage type.  Two steps per launch
-// halve the state traffic but recompute the first step on the patch ring
-// (18-37% more collisions); FP32 comes out even, FP16 (bound by arithmetic)
-// and FP64 (whose Newton solve dominates once the whole cavity moves) lose.
-// The two-step defaults below are the best measured shapes.
 // Velocity output subtracts F/2 from the momentum of the stored state: right
 // for post-collision populations (two-buffer form); the in-place form stores
 // pre-collision populations, whose momentum needs + F/2.
@@ -55,6 +51,49 @@ static void set_step(clbm_lattice *h, int64_t step) {
     h->rd.step = h->rf.step = (uint32_t)step;
 }
 
+// Whether pairs of steps run faster as one two-step launch, and its z chunk.
+//
+// The two-step kernel halves the state traffic but takes whole 62 x 14 column
+// patches and recomputes their rims, so it gains where the patches of the
+// lattice fill rounds of one workgroup per compute unit: a round of chunks of
+// c planes takes (c + 2) plane steps of 7.1 us (256^3) to 7.9 us (512^3).
+// Against it, one step per launch moves 152 bytes per node at 5.65 TB/s (rows of
+// whole 64-byte pieces), 5.0 TB/s (others) or 6.8 TB/s (both states within the
+// last-level cache).  Measured, FP32, us per step: 256^3 382 against 450,
+// 300 x 280 x 290 558 against 733, 200 x 190 x 220 224 against 250, 160^3 104
+// against 110; not taken at 192^3 (195 against 189) and 128^3 (66 against 58).
+// Chunks beyond 16 planes lose the cache lines that neighbouring patches share
+// (512^3: 2.98 ms at 16, 3.06 at 32).  FP16 and FP64 lose (bound by arithmetic),
+// the forced kernel spills registers, a periodic z axis is not pipelined.
+static bool pair_launch(const clbm_params *p, size_t bytes, bool forced, int route, StepLaunch *c) {
+    if (p->storage != CLBM_F32 || p->layout != CLBM_LAYOUT_ROWS || forced || route != 0 || p->periodic[2]) return false;
+    if ((uint64_t)Q * 4u * (uint64_t)p->nx * (uint64_t)p->ny * 8u >= 0x80000000ull) return false;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        return false;
+    const int64_t columns = (int64_t)((p->nx + 61) / 62) * ((p->ny + 13) / 14);
+    int64_t best = INT64_MAX;
+    int planes = 16;
+    for (int k = 6; k <= 16; ++k) {
+        const int64_t rounds = (columns * ((p->nz + k - 1) / k) + cus - 1) / cus;
+        if (rounds * (k + 2) <= best) {
+            best = rounds * (k + 2);
+            planes = k;
+        }
+    }
+    const double rate = 2 * bytes <= ((size_t)256 << 20) ? 6.8 : ((int64_t)p->nx * 4 % 64 == 0 ? 5.65 : 5.0);
+    const double one_us = 2.0 * (double)bytes / (rate * 1e6), two_us = 0.5 * 7.6 * (double)best;
+    if (two_us > 0.97 * one_us) return false;
+    c->fuse_steps = 2;
+    c->fuse_rows = 16;
+    c->fuse_planes = planes;
+    c->xcd_remap = 1;
+    c->nt_stores = 0;
+    return true;
+}
+
+// The two-step shape that a launch configuration starts from.
 static void default_fusion(const clbm_params *p, StepLaunch *c) {
     const bool f64 = p->storage == CLBM_F64;
     c->fuse_steps = 1;
@@ -194,6 +233,8 @@ static clbm_status create_common(const clbm_params *p, void *pop_a, void *pop_b,
     h->cur = 0;
     default_launch(p, need, &h->launch);
     default_fusion(p, &h->launch);
+    h->pair = h->launch;
+    h->pair_steps = !in_place && !flags && pair_launch(p, need, h->forced, h->route, &h->pair);
 
     const int64_t N = (int64_t)p->nx * p->ny * p->nz;
     int64_t nb = (N + kReduceThreads - 1) / kReduceThreads;
@@ -333,11 +374,12 @@ clbm_status clbm_step(clbm_lattice *h, int64_t nsteps, void *stream) {
         return CLBM_OK;
     }
     int64_t t = 0;
-    if (h->launch.fuse_steps == 2) {
+    if (h->launch.fuse_steps == 2 || h->pair_steps) {
+        const StepLaunch &two = h->pair_steps ? h->pair : h->launch;
         for (; t + 2 <= nsteps; t += 2) {
             set_step(h, h->steps_done + 1);
             HIP_TRY(launch_step2(h->prm.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geom, h->rd, h->rf,
-                                 h->forced, h->route, h->launch, st),
+                                 h->forced, h->route, two, st),
                     "clbm_step (two-step launch)");
             h->cur = 1 - h->cur;
             h->steps_done += 2;
@@ -450,6 +492,7 @@ clbm_status clbm_set_launch(clbm_lattice *h, const clbm_launch *c) {
     h->launch.fuse_steps = c->fuse_steps;
     h->launch.fuse_rows = c->fuse_rows;
     h->launch.fuse_planes = c->fuse_planes;
+    h->pair_steps = false;
     return CLBM_OK;
 }
 
@@ -558,6 +601,7 @@ clbm_status clbm_autotune(clbm_lattice *h, void *stream, clbm_launch *best, doub
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return hip_fail(e, "autotune: trial launch");
     h->launch = win;
+    h->pair_steps = false;
     if (best) clbm_get_launch(h, best);
     if (best_ms) *best_ms = win_ms;
     return CLBM_OK;

@@ -75,3 +75,26 @@ def test_reductions_at_block_edges(clbm, nodes):
     for k in ("mass", "momentum_x", "momentum_y", "momentum_z", "umax", "kinetic"):
         assert again[k] == r[k]         # the same order of additions
     lat.close()
+
+
+@pytest.mark.parametrize("shape,steps", [((248, 238, 240), 5), ((187, 169, 250), 4)])
+def test_default_pairs_of_steps_match_single_steps(clbm, shape, steps):
+    """FP32 lattices large enough that pairs of steps run as two-step launches
+    by default (an odd remainder as one step), against one step per launch: the
+    operations of both are the same up to the compiler's choice of fused
+    multiply-adds (bound of the two-step tests)."""
+    nx, ny, nz = shape
+    spec = W.cavity(64, 0.05, 0.8, 300.0).with_(nx=nx, ny=ny, nz=nz)
+    print(f"[gpu] default pairs {shape}", flush=True)
+    f0 = W.perturbed_populations(spec, 3, 1e-2, device="cuda")
+    outs = []
+    for launch in (None, {"fuse_steps": 1}):
+        lat = clbm.Lattice(spec, storage="f32", track_residual=False, launch=launch)
+        lat.init_populations(f0)
+        lat.step(steps)
+        idx, done = lat.state()
+        assert done == steps and idx == ((steps + 1) // 2 if launch is None else steps) % 2
+        outs.append(lat.state_view().clone())
+        lat.close()
+    worst = max((outs[0][k] - outs[1][k]).abs().max().item() for k in range(19))
+    assert worst <= 1e-5 * outs[1].abs().max().item()
