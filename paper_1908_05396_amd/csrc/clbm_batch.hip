@@ -76,8 +76,8 @@ batch_step_kernel(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T>
 // the full wall rule by address selects as in the single-lattice flat kernel:
 // no idle lanes but in an instance's last item, and no separate faces.
 //
-// Bound: HBM and issue.  64 cavities of edge 32 to 96, FP32: 617 us per
-// step, 5.3 TB/s (682 with an item per run of a row, the short tails of two
+// Bound: HBM and issue.  64 cavities of edge 32 to 96, FP32: 638 us per
+// step, 5.1 TB/s (682 with an item per run of a row, the short tails of two
 // rows sharing a wave: 1.19 lanes per node and a second round of loads for the
 // x faces).
 template <typename S, typename T, int Route, int StAux, bool AnyForced>
@@ -480,8 +480,8 @@ clbm_status clbm_batch_create(const clbm_params *inst, int32_t count, void *pool
     b->pool[0] = pool_a;
     b->pool[1] = pool_b;
     b->bytes_each = bytes_each;
-    // row layout: 256 threads (64-cavity mix, FP32: 617 us per step, 650 at 512, 669 at 128; FP16, bound by
-    // arithmetic, 411 at 512, 418 at 256)
+    // row layout: 256 threads (64-cavity mix, FP32: 638 us per step, 673 at 512; FP16, bound by
+    // arithmetic, 397 at 512)
     b->cfg.bx = b->rows && b->storage != CLBM_F16_DEV ? 256 : max_threads(b);
     b->cfg.by = 1;
     b->cfg.blocks_per_cu = 1024;    // capped at one item per wave (row layout) or one tile per workgroup

@@ -1,4 +1,4 @@
-// Row layout helpers shared by the two-buffer and in-place row kernels.
+// Row layout helpers shared by the single-lattice, in-place, flagged and batch kernels.
 //
 // Row layout: the 19 populations of lattice row r = y + ny z are 19
 // consecutive runs of nx values, population a of node x at element
@@ -70,9 +70,7 @@ inline uint32_t all_rows(const Geom &g, int threads, int remap, RowGrid &R) {
 
 // Row kernels group the x-face bounce-back loads of a wave (row_gather's
 // XGroup) with FP32 storage: at 512^3 the one-step launch runs 1.3% and the
-// two-step one 2.9% faster, the 64-cavity batch 2.8% (its waves all hold face
-// lanes; compiled at seven waves per SIMD, since the grouped loads need more
-// than the 64 VGPRs of eight).  FP16 storage, bound by its arithmetic, ran 3%
+// two-step one 2.9% faster.  FP16 storage, bound by its arithmetic, ran 3%
 // slower that way and keeps the per-direction path.
 template <typename S> struct XGroupRows { static constexpr bool value = std::is_same<S, float>::value; };
 
