@@ -1,5 +1,5 @@
-"""The row layout's flat step kernel at the edges of its addressing, and the
-reductions at the edges of their block counts.
+"""The row layout's flat kernels at the edges of their addressing, the default
+pairs of steps, and the reductions at the edges of their block counts.
 
 The flat kernel takes 64 consecutive nodes per wave and addresses sources by
 32-bit offsets: from the start of the state below 1 GiB (FP32, FP64), else from
@@ -98,3 +98,34 @@ def test_default_pairs_of_steps_match_single_steps(clbm, shape, steps):
         lat.close()
     worst = max((outs[0][k] - outs[1][k]).abs().max().item() for k in range(19))
     assert worst <= 1e-5 * outs[1].abs().max().item()
+
+
+@pytest.mark.parametrize("form", ["flagged", "in_place"])
+def test_far_addressing_of_flagged_and_one_buffer_lattices(clbm, form):
+    """A state beyond 4 GiB with a periodic z axis: offsets from the wave's own
+    layer, and 64-bit addresses across the z faces, against the planes layout."""
+    nx, ny, nz = 70, 9, 45003
+    spec = W.LatticeSpec(nx=nx, ny=ny, nz=nz, K=0.02, n=0.8, periodic=(1, 0, 1), lid_face=W.LID_PY,
+                         lid_velocity=(0.04, 0.0, 0.01), name="far")
+    assert 19 * 8 * spec.nodes > 2 ** 32
+    kw = {}
+    if form == "flagged":
+        flags = torch.zeros((nz, ny, nx), dtype=torch.uint8, device="cuda")
+        flags[0, 2:4, 10:20] = 1            # solid nodes on both z faces: sources across the wrap
+        flags[nz - 1, 5:7, 30:50] = 2
+        flags[1000:1010, 1:3, 60:70] = 1
+        kw = dict(flags=flags)
+    else:
+        kw = dict(in_place=True)
+    print(f"[gpu] far {form}", flush=True)
+    f0 = W.perturbed_populations(spec, 8, 1e-2, device="cuda")
+    outs = []
+    for layout in ("rows", "planes"):
+        lat = clbm.Lattice(spec, storage="f64", track_residual=False, layout=layout, **kw)
+        lat.init_populations(f0)
+        lat.step(4)
+        outs.append(lat.state_view().clone())
+        lat.close()
+    scale = max(outs[1][k].abs().max().item() for k in range(19))
+    worst = max((outs[0][k] - outs[1][k]).abs().max().item() for k in range(19))
+    assert worst <= 1e-13 * scale
