@@ -231,8 +231,13 @@ clbm_status clbm_init_populations(clbm_lattice *h, const double *f0, int on_devi
  * collision with the local relaxation rate of Sec. 3.2, then streaming,
  * Eq. cascaded streaming, with the wall rules of Sec. 4): one fused pull
  * stream-collide launch per step (two steps per launch with fuse_steps = 2, or
- * by the library's choice while no launch configuration has been set;
- * in the in-place form one launch per step and nsteps even).  Asynchronous;
+ * by the library's choice, four steps at a time, while no launch configuration
+ * has been set; in the in-place form one launch per step and nsteps even).
+ * Without fuse_steps = 2 the state moves to the other buffer at every step,
+ * also where the library chose two-step launches, so a call of an even number
+ * of steps ends in the buffer it began with: captured into a HIP graph, it can
+ * be replayed.  With fuse_steps = 2 it moves once per pair of steps, and a
+ * captured call has to be a multiple of four steps for that.  Asynchronous;
  * no host synchronization, no allocation, no NaN check (clbm_reduce does
  * that).  EINVAL for nsteps < 0, ESTATE before an init call. */
 clbm_status clbm_step(clbm_lattice *h, int64_t nsteps, void *stream);
@@ -312,10 +317,11 @@ typedef struct {
 } clbm_launch;
 
 /* Until a configuration is set (clbm_set_launch, clbm_set_block,
- * clbm_autotune), clbm_step may run pairs of steps of FP32 row-layout lattices
- * as two-step launches of its own choice where these run faster;
+ * clbm_autotune), clbm_step may run FP32 row-layout lattices four steps at a
+ * time as two two-step launches of its own choice where these run faster;
  * clbm_get_launch reports the one-step configuration that it uses otherwise
- * (and for an odd remainder). */
+ * (and for the remaining one to three steps).  Setting any configuration, that
+ * one included, ends it. */
 clbm_status clbm_set_launch(clbm_lattice *h, const clbm_launch *cfg);
 clbm_status clbm_get_launch(clbm_lattice *h, clbm_launch *cfg);
 

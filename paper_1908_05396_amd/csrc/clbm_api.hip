@@ -26,7 +26,7 @@ struct clbm_lattice {
     bool initialized;
     int64_t steps_done;
     StepLaunch launch;
-    bool pair_steps;        // until a launch is set: pairs of steps run as two-step launches of shape `pair`
+    bool pair_steps;        // until a launch is set: four steps run as two two-step launches of shape `pair`
     StepLaunch pair;
     // reduction scratch (library-owned)
     double *partials;
@@ -374,16 +374,19 @@ clbm_status clbm_step(clbm_lattice *h, int64_t nsteps, void *stream) {
         return CLBM_OK;
     }
     int64_t t = 0;
-    if (h->launch.fuse_steps == 2 || h->pair_steps) {
-        const StepLaunch &two = h->pair_steps ? h->pair : h->launch;
-        for (; t + 2 <= nsteps; t += 2) {
-            set_step(h, h->steps_done + 1);
-            HIP_TRY(launch_step2(h->prm.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geom, h->rd, h->rf,
-                                 h->forced, h->route, two, st),
-                    "clbm_step (two-step launch)");
-            h->cur = 1 - h->cur;
-            h->steps_done += 2;
-        }
+    // Pairs of the library's own choice come two at a time, four steps: the
+    // state then ends in the buffer that single steps leave it in, whatever
+    // nsteps is, so that a captured call of an even number of steps can be
+    // replayed on its own result.
+    const int64_t paired = h->pair_steps ? nsteps / 4 * 4 : h->launch.fuse_steps == 2 ? nsteps / 2 * 2 : 0;
+    const StepLaunch &two = h->pair_steps ? h->pair : h->launch;
+    for (; t < paired; t += 2) {
+        set_step(h, h->steps_done + 1);
+        HIP_TRY(launch_step2(h->prm.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geom, h->rd, h->rf, h->forced,
+                             h->route, two, st),
+                "clbm_step (two-step launch)");
+        h->cur = 1 - h->cur;
+        h->steps_done += 2;
     }
     for (; t < nsteps; ++t) {
         set_step(h, h->steps_done + 1);
