@@ -233,7 +233,8 @@ clbm_status clbm_init_populations(clbm_lattice *h, const double *f0, int on_devi
  * stream-collide launch per step (two steps per launch with fuse_steps = 2, or
  * by the library's choice, four steps at a time, while no launch configuration
  * has been set; in the in-place form one launch per step and nsteps even).
- * Without fuse_steps = 2 the state moves to the other buffer at every step,
+ * Without fuse_steps = 2 the result is the same, bit for bit, however the steps
+ * are split over calls, and the state moves to the other buffer at every step,
  * also where the library chose two-step launches, so a call of an even number
  * of steps ends in the buffer it began with: captured into a HIP graph, it can
  * be replayed.  With fuse_steps = 2 it moves once per pair of steps, and a

@@ -771,11 +771,17 @@ __device__ inline bool ghost_in_lid(const Geom &g, int sx, int sy, int sz) {
 // Half-way bounce-back along e_a: the node's own post-collision population
 // opposite to a (w_a = w_opp(a), so the deviation carries over), plus the
 // moving-wall term w_a 6 rho_w (e_a . U_w) for a ghost in the lid plane.
+// The term is added by an explicit fused multiply-add (the sum in brackets has
+// one rounding in any form): left to the compiler, kernels that hoist the
+// product out of a loop round it once more, and two steps in one launch
+// differ in the last bit from two launches.
+__device__ inline float fused_madd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fused_madd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <typename T>
 __device__ inline T wall_value(T own_opposite, const Relax<T> &p, int a, bool in_lid) {
-    T v = own_opposite;
-    if (in_lid) v += (T)weight(a) * (T(cx(a)) * p.lid6[0] + T(cy(a)) * p.lid6[1] + T(cz(a)) * p.lid6[2]);
-    return v;
+    const T eu = T(cx(a)) * p.lid6[0] + T(cy(a)) * p.lid6[1] + T(cz(a)) * p.lid6[2];
+    return in_lid ? fused_madd((T)weight(a), eu, own_opposite) : own_opposite;
 }
 
 // Pull along one direction with the full wall logic (used for lanes on the

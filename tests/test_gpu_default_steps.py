@@ -1,7 +1,7 @@
 """The two-step launches that clbm_step chooses by itself for FP32 row-layout
-lattices: the state ends in the buffer that single steps leave it in, however
-the steps are split over calls, and a captured call of an even number of steps
-can be replayed."""
+lattices: the state ends in the buffer that single steps leave it in, with the
+same bits, however the steps are split over calls, and a captured call of an
+even number of steps can be replayed."""
 import pytest
 import torch
 
@@ -87,3 +87,29 @@ def test_captured_steps_replay(clbm, k):
     assert torch.equal(lat.state_view(), ref.state_view())
     ref.close()
     lat.close()
+
+
+LIDS = {W.LID_MX: (0.0, 0.03, 0.02), W.LID_PX: (0.0, 0.03, -0.02), W.LID_MY: (0.03, 0.0, 0.02),
+        W.LID_PY: (0.05, 0.0, 0.0), W.LID_MZ: (0.03, 0.02, 0.0), W.LID_PZ: (0.03, -0.02, 0.0)}
+
+
+@pytest.mark.parametrize("shape,periodic,lid",
+                         [((160, 160, 160), (0, 0, 0), lid) for lid in LIDS] +
+                         [((201, 191, 221), (1, 0, 0), W.LID_PY), ((201, 191, 221), (0, 1, 0), W.LID_MX),
+                          ((160, 160, 160), (1, 1, 0), W.LID_MZ), ((62, 14, 4000), (1, 1, 0), W.LID_PZ),
+                          ((160, 160, 160), (1, 1, 0), W.LID_NONE)])
+def test_results_do_not_depend_on_the_split(clbm, shape, periodic, lid):
+    """Eight steps in one call (two-step launches), in calls of 5 and 3, and one
+    by one: the same operations with the same roundings, so the same bits."""
+    spec = _box(*shape, periodic=periodic, lid_face=lid, lid_velocity=LIDS.get(lid, (0.0, 0.0, 0.0)))
+    print(f"[gpu] default split {shape} periodic {periodic} lid {lid}", flush=True)
+    f0 = W.perturbed_populations(spec, 6, 1e-2, device="cuda")
+    outs = []
+    for calls in ((8,), (5, 3), (1,) * 8):
+        lat = clbm.Lattice(spec, storage="f32", track_residual=False)
+        lat.init_populations(f0)
+        for k in calls:
+            lat.step(k)
+        outs.append(lat.state_view().clone())
+        lat.close()
+    assert torch.equal(outs[0], outs[2]) and torch.equal(outs[1], outs[2])
