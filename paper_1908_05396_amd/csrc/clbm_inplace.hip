@@ -215,55 +215,53 @@ aa_odd_flat_kernel(S *__restrict__ A, Geom g, Relax<T> p, FlatGrid L) {
     }
 }
 
-// Even and odd steps at one node with the full wall rule per lane, in either
-// layout (layers beyond the reach of 32-bit offsets).
+// The same steps for layers beyond the reach of 32-bit offsets, one thread per
+// node at any width (with a workgroup per run of a row, the lanes beyond the row
+// idle, 2^24 narrow rows need more than the 2^32 threads that a launch can have,
+// and the runtime starts the remainder only, without an error).  us per step of ten layers: 20 x 395 000 FP32
+// 2753 against 8275, 70 x 56 000 FP64 2322 against 8047, 2000 x 7 900 FP16 2154
+// against 4697.
 template <typename S, typename T, bool Forced, int Route>
-__device__ inline void aa_even_any(S *__restrict__ A, const Geom &g, const Relax<T> &p, int x, int y, int z) {
-    T d[Q];
-#pragma unroll
-    for (int a = 0; a < Q; ++a) d[a] = (T)Conv<S, T>::load(A[elem(g, a, x, y, z)]);
-    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    round_state<S, T>(d, p, (uint32_t)x + (uint32_t)g.nx * ((uint32_t)y + (uint32_t)g.ny * (uint32_t)z), p.step);
-#pragma unroll
-    for (int a = 0; a < Q; ++a) A[elem(g, opp(a), x, y, z)] = Conv<S, T>::store(d[a]);
-}
-
-template <typename S, typename T, bool Forced, int Route>
-__device__ inline void aa_odd_any(S *__restrict__ A, const Geom &g, const Relax<T> &p, int x, int y, int z) {
-    T d[Q];
-#pragma unroll
-    for (int a = 0; a < Q; ++a) {
-        int sx = x - cx(a), sy = y - cy(a), sz = z - cz(a);
-        const bool in_lid = ghost_in_lid(g, sx, sy, sz);
-        const bool ok = wrap(sx, g.nx, g.px) & wrap(sy, g.ny, g.py) & wrap(sz, g.nz, g.pz);
-        d[a] = ok ? (T)Conv<S, T>::load(A[elem(g, opp(a), sx, sy, sz)])
-                  : wall_value<T>((T)Conv<S, T>::load(A[elem(g, a, x, y, z)]), p, a, in_lid);
-    }
-    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
-    round_state<S, T>(d, p, (uint32_t)x + (uint32_t)g.nx * ((uint32_t)y + (uint32_t)g.ny * (uint32_t)z), p.step);
-#pragma unroll
-    for (int a = 0; a < Q; ++a) {
-        int tx = x + cx(a), ty = y + cy(a), tz = z + cz(a);
-        const bool in_lid = ghost_in_lid(g, tx, ty, tz);
-        const bool ok = wrap(tx, g.nx, g.px) & wrap(ty, g.ny, g.py) & wrap(tz, g.nz, g.pz);
-        if (ok)
-            A[elem(g, a, tx, ty, tz)] = Conv<S, T>::store(d[a]);
-        else
-            A[elem(g, opp(a), x, y, z)] = Conv<S, T>::store(wall_value<T>(d[a], p, opp(a), in_lid));
-    }
-}
-
-// any block shape, row layout: every node with the full rule
-template <typename S, typename T, bool Forced, int Route, bool Odd>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
-aa_any_kernel(S *__restrict__ A, Geom g, Relax<T> p, LaunchGrid L) {
-    int x, y, z;
-    locate(L, x, y, z);
-    if (x >= g.nx || y >= g.ny) return;
-    if (Odd)
-        aa_odd_any<S, T, Forced, Route>(A, g, p, x, y, z);
-    else
-        aa_even_any<S, T, Forced, Route>(A, g, p, x, y, z);
+aa_even_wide_kernel(S *__restrict__ A, Geom g, Relax<T> p, FlatGrid L) {
+    const FlatLane<S, true> k(g, L);
+    if (k.i >= (uint32_t)g.n) return;
+    S *own = A + WideNode<S>(g, k.x, k.y, k.z).own;
+    T d[Q];
+#pragma unroll
+    for (int a = 0; a < Q; ++a) d[a] = (T)Conv<S, T>::load(own[(int64_t)a * g.nx]);
+    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
+    round_state<S, T>(d, p, k.i, p.step);
+#pragma unroll
+    for (int a = 0; a < Q; ++a) own[(int64_t)opp(a) * g.nx] = Conv<S, T>::store(d[a]);
+}
+
+template <typename S, typename T, bool Forced, int Route>
+__global__ void __launch_bounds__(MaxThreads<T>::value)
+aa_odd_wide_kernel(S *__restrict__ A, Geom g, Relax<T> p, FlatGrid L) {
+    const FlatLane<S, true> k(g, L);
+    if (k.i >= (uint32_t)g.n) return;
+    T d[Q];
+    {
+        const WideNode<S> w(g, k.x, k.y, k.z);
+#pragma unroll
+        for (int a = 0; a < Q; ++a) d[a] = (T)Conv<S, T>::load(A[w.at(a, opp(a))]);
+        if (w.f.wave_touches_lid()) {
+#pragma unroll
+            for (int a = 1; a < Q; ++a) d[a] = wall_value<T>(d[a], p, a, w.f.lid(a));
+        }
+    }
+    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
+    round_state<S, T>(d, p, k.i, p.step);
+    int x = k.x, y = k.y, z = k.z;      // the addresses once more, as in aa_odd_flat_kernel
+    asm volatile("" : "+v"(x), "+v"(y), "+v"(z));
+    const WideNode<S> w(g, x, y, z);
+    if (w.f.wave_touches_lid()) {
+#pragma unroll
+        for (int a = 1; a < Q; ++a) d[a] = wall_value<T>(d[a], p, opp(a), w.f.lid(opp(a)));
+    }
+#pragma unroll
+    for (int a = 0; a < Q; ++a) A[w.at(opp(a), a)] = Conv<S, T>::store(d[a]);
 }
 
 template <typename S, typename T, bool Forced, int Route, bool Far>
@@ -287,6 +285,15 @@ static hipError_t aa_pair_f(void *A, const Geom &g, const Relax<T> &p, const Ste
         const FlatLaunch F = flat_launch(g, sizeof(S), threads, c.xcd_remap);
         if (F.near) return aa_pair_flat<S, T, Forced, Route, false>(A, g, p, F, threads, st);
         if (F.far) return aa_pair_flat<S, T, Forced, Route, true>(A, g, p, F, threads, st);
+        Relax<T> q = p;         // the odd step is the next collision
+        q.step = p.step + 1u;
+        hipLaunchKernelGGL((aa_even_wide_kernel<S, T, Forced, Route>), dim3(F.blocks), dim3(threads), 0, st, (S *)A, g, p,
+                           F.grid);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((aa_odd_wide_kernel<S, T, Forced, Route>), dim3(F.blocks), dim3(threads), 0, st, (S *)A, g, q,
+                           F.grid);
+        return hipGetLastError();
     }
     LaunchGrid L;
     L.gx = (g.nx + c.bx - 1) / c.bx;
@@ -298,13 +305,6 @@ static hipError_t aa_pair_f(void *A, const Geom &g, const Relax<T> &p, const Ste
     dim3 grid(nb), block(c.bx, c.by);
     Relax<T> q = p;             // the odd step is the next collision
     q.step = p.step + 1u;
-    if (g.rows) {
-        hipLaunchKernelGGL((aa_any_kernel<S, T, Forced, Route, false>), grid, block, 0, st, (S *)A, g, p, L);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((aa_any_kernel<S, T, Forced, Route, true>), grid, block, 0, st, (S *)A, g, q, L);
-        return hipGetLastError();
-    }
     hipLaunchKernelGGL((aa_even_kernel<S, T, Forced, Route>), grid, block, 0, st, (S *)A, g, p, L);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

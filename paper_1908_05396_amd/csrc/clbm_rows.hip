@@ -11,6 +11,8 @@
 //                         per-lane source addresses: no idle lanes at any
 //                         width, no second launch or second round of loads for
 //                         the faces.
+//   stream_collide_rows_wide   the same with 64-bit offsets, for layers beyond
+//                         the reach of 32-bit ones.
 //   stream_collide_rows   large FP32 lattices: each wave covers 64 consecutive
 //                         x of one row, so a direction's source is a uniform
 //                         address plus the lane's x; rows on a y or z face
@@ -60,6 +62,31 @@ stream_collide_rows_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, R
     row_store<S, T, StAux>(B, g, x, y, z, d, p.sr != 0, sr_base(node, p.step));
 }
 
+// The flat kernel for layers beyond the reach of 32-bit offsets, in FP64 and
+// FP16, and in FP32 below 64 columns (a wave per row would leave its lanes idle
+// and, from 2^26 rows, need more than the 2^32 threads that a launch can have:
+// the runtime starts the remainder only, without an error).  us per step, against the kernel with a wave per row: ten layers of
+// 20 x 195 000 FP64 2407 against 6150, 70 x 112 000 FP16 2874 against 8319,
+// 2000 x 7 900 FP16 2205 against 4602.
+template <typename S, typename T, bool Forced, int Route>
+__global__ void __launch_bounds__(MaxThreads<T>::value)
+stream_collide_rows_wide_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, FlatGrid L) {
+    const FlatLane<S, true> k(g, L);
+    if (k.i >= (uint32_t)g.n) return;
+    const WideNode<S> w(g, k.x, k.y, k.z);
+    T d[Q];
+#pragma unroll
+    for (int a = 0; a < Q; ++a) d[a] = (T)Conv<S, T>::load(A[w.at(a, a)]);
+    if (w.f.wave_touches_lid()) {
+#pragma unroll
+        for (int a = 1; a < Q; ++a) d[a] = wall_value<T>(d[a], p, a, w.f.lid(a));
+    }
+    collide<T, Forced, Route, NewtonSteps<S>::value>(d, p, nullptr);
+    round_state<S, T>(d, p, k.i, p.step);
+#pragma unroll
+    for (int a = 0; a < Q; ++a) B[w.own + a * w.run] = Conv<S, T>::store(d[a]);
+}
+
 template <typename S, typename T, bool Forced, int LdAux, int StAux, int Route>
 static hipError_t launch_rows_k(const S *a, S *b, const Geom &g, const Relax<T> &p, const StepLaunch &c,
                                 hipStream_t st) {
@@ -69,7 +96,8 @@ static hipError_t launch_rows_k(const S *a, S *b, const Geom &g, const Relax<T> 
     // own layer (300 x 280 x 290: 733 against 772 us FP32, 1220 against 1299
     // FP64), FP16 between 3% faster and 4% slower.  From 4 GiB FP32 runs 2-6%
     // faster with one wave per run of a row (512^3 3449 against 3524 us; 500^3,
-    // whole rows per workgroup, 3569 against 3784), FP64 and FP16 1-14% slower.
+    // whole rows per workgroup, 3569 against 3784; between 65 and 400 columns,
+    // 5.2 GB, as fast: 1924 against 1893 us at 100), FP64 and FP16 1-14% slower.
     const bool prefer_far = !std::is_same<S, __half>::value && (uint64_t)Q * sizeof(S) * (uint64_t)g.n > (1ull << 30);
     const bool prefer_rows = std::is_same<S, float>::value && !L.near && g.nx >= 64;
     if (!prefer_rows && (L.near || L.far)) {
@@ -79,6 +107,11 @@ static hipError_t launch_rows_k(const S *a, S *b, const Geom &g, const Relax<T> 
         else
             hipLaunchKernelGGL((stream_collide_rows_flat_kernel<S, T, Forced, LdAux, StAux, Route, true>),
                                dim3(L.blocks), dim3(threads), 0, st, a, b, g, p, L.grid);
+        return hipGetLastError();
+    }
+    if (!prefer_rows) {
+        hipLaunchKernelGGL((stream_collide_rows_wide_kernel<S, T, Forced, Route>), dim3(L.blocks), dim3(threads), 0, st, a,
+                           b, g, p, L.grid);
         return hipGetLastError();
     }
     RowGrid R;

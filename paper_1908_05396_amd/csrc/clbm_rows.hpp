@@ -383,4 +383,28 @@ template <typename S, bool Far> struct FlatLane {
     }
 };
 
+// Layers beyond the reach of 32-bit offsets (430 MB and more): the same selects
+// on 64-bit element offsets from the start of the state.
+template <typename S> struct WideNode {
+    FlatNode<S, true> f;                    // faces, walls and lid
+    int64_t run, own, xm, xp, ym, yp, zm, zp;   // elements
+    __device__ __forceinline__ WideNode(const Geom &g, int x, int y, int z) : f(g, 0u, x, y, z) {
+        run = g.nx;
+        const int64_t row = g.row, layer = row * g.ny, lattice = layer * g.nz;
+        own = z * layer + y * row + x;
+        xm = f.hi[0] ? 1 - run : 1;
+        xp = f.lo[0] ? run - 1 : -1;
+        ym = f.hi[1] ? row - layer : row;
+        yp = f.lo[1] ? layer - row : -row;
+        zm = f.hi[2] ? layer - lattice : layer;
+        zp = f.lo[2] ? lattice - layer : -layer;
+    }
+    // run `slot` of the source of direction a; beyond a wall the node's own run of the opposite direction
+    __device__ __forceinline__ int64_t at(int a, int slot) const {
+        const int64_t d = (cx(a) == 0 ? 0 : cx(a) == 1 ? xp : xm) + (cy(a) == 0 ? 0 : cy(a) == 1 ? yp : ym) +
+                          (cz(a) == 0 ? 0 : cz(a) == 1 ? zp : zm);
+        return own + (f.wall(a) ? opp(slot) * run : d + slot * run);
+    }
+};
+
 }  // namespace clbm
