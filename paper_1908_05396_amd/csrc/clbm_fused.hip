@@ -190,8 +190,8 @@ struct FusedGrid {
 };
 
 // StAux: cache hint of the population stores (0 plain, 2 non-temporal);
-// Rows: row layout (else planes); Pipe: its loads a plane ahead (no periodic z
-// axis, eight layers within 2^31 bytes)
+// Rows: row layout (else planes); Pipe: its loads a plane ahead (FP32, no
+// periodic z axis, eight layers within 2^31 bytes)
 template <typename S, typename T, bool Forced, int Route, int ROWS, bool PF, int StAux, bool Rows, bool Pipe>
 __global__ void __launch_bounds__(kLanes * ROWS)
 stream_collide2_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax<T> p, FusedGrid L) {
@@ -420,9 +420,16 @@ static hipError_t launch2_f(const void *A, void *B, const Geom &g, const Relax<T
     if (nb == 0 || nb > 0x7fffffffull) return hipErrorInvalidValue;
     L.aligned = (uint32_t)nb & ~7u;
     L.remap = c.xcd_remap;
-    const bool pipe = Rows && !g.pz && (uint64_t)Q * sizeof(S) * (uint64_t)g.nxy * 8u < 0x80000000ull;
-    auto k = pipe ? (c.nt_stores ? stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 2, Rows, Rows>
-                                 : stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 0, Rows, Rows>)
+    // Loads a plane ahead with FP32 storage alone: they take 19 registers more.
+    // us per step without and with them, 200 x 190 x 220: FP32 16 rows 259 and
+    // 252, 8 rows 220 and 206 (without: with a periodic z axis); FP64 676 and
+    // 706, forced 708 and 770, printed form 841 and 993 (spilled); FP16 8 rows
+    // 259 and 345, 16 rows 305 and 287, with a periodic x axis 241 and 258, 256^3
+    // 434 and 441.
+    constexpr bool kPipe = Rows && std::is_same<S, float>::value;
+    const bool pipe = kPipe && !g.pz && (uint64_t)Q * sizeof(S) * (uint64_t)g.nxy * 8u < 0x80000000ull;
+    auto k = pipe ? (c.nt_stores ? stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 2, Rows, kPipe>
+                                 : stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 0, Rows, kPipe>)
                   : (c.nt_stores ? stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 2, Rows, false>
                                  : stream_collide2_kernel<S, T, Forced, Route, ROWS, PF, 0, Rows, false>);
     hipLaunchKernelGGL(k, dim3((uint32_t)nb), dim3(kLanes * ROWS), 0, st, (const S *)A, (S *)B, g, p, L);
