@@ -240,12 +240,11 @@ macroscopic_kernel(const S *__restrict__ A, const uint8_t *__restrict__ flags, O
         uy = (jy - 0.5 * fy) / r;
         uz = (jz - 0.5 * fz) / r;
     }
-    // (streaming stores: 200 x 160 x 130 FP32 73 against 82 us with FP64 output)
-    if (rho) __builtin_nontemporal_store((O)r, rho + i);
+    if (rho) rho[i] = (O)r;
     if (u) {
-        __builtin_nontemporal_store((O)ux, u + i);
-        __builtin_nontemporal_store((O)uy, u + N + i);
-        __builtin_nontemporal_store((O)uz, u + 2 * N + i);
+        u[i] = (O)ux;
+        u[N + i] = (O)uy;
+        u[2 * N + i] = (O)uz;
     }
 }
 
@@ -257,9 +256,8 @@ export_kernel(const S *__restrict__ A, double *__restrict__ f, Geom g) {
     if (i >= N) return;
 #pragma unroll
     for (int a = 0; a < Q; ++a)
-        __builtin_nontemporal_store(    // 168 against 177 us at 200 x 160 x 130 FP32
-            weight(a) + (double)Conv<S, typename StoreCompute<S>::T>::load(A[elem_i(g, a, i)]),
-            f + (int64_t)a * N + i);
+        f[(int64_t)a * N + i] =
+            weight(a) + (double)Conv<S, typename StoreCompute<S>::T>::load(A[elem_i(g, a, i)]);
 }
 
 // ---------------------------------------------------------------------------
