@@ -367,7 +367,8 @@ typedef struct clbm_batch clbm_batch;
 
 typedef struct {
     int32_t bx, by;            /* threads per workgroup, a multiple of 64, <= 512 (<= 256 for FP64;
-                                  default: that maximum, 256 in the row layout with FP32 storage);
+                                  default: that maximum, 256 in the row layout with FP32 storage
+                                  where the grid then reaches one item per wave);
                                   planes: the tile is bx consecutive nodes of one z layer (x fastest);
                                   rows: bx / 64 waves, each on its own items; by must be 1 */
     int32_t blocks_per_cu;     /* grid = blocks_per_cu x CUs workgroups (1..1024), at most one item

@@ -102,8 +102,8 @@ __device__ __forceinline__ void batch_nodes(const S *__restrict__ A, S *__restri
 }
 
 // Loop: a wave strides over items, or an item holds several groups of nodes.
-// Without it (one item of 64 nodes per wave, the default) the compiler keeps
-// no loop-invariant constants alive: 62 instead of 86 VGPRs in FP32.
+// Without it (one item of 64 nodes per wave, the default) the code is a twelfth
+// shorter and keeps no loop state (forced FP32 80 instead of 88 VGPRs).
 template <typename S, typename T, int Route, int StAux, bool AnyForced, bool Loop>
 __global__ void __launch_bounds__(MaxThreads<T>::value)
 batch_rows_kernel(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T> *__restrict__ inst,
@@ -480,9 +480,6 @@ clbm_status clbm_batch_create(const clbm_params *inst, int32_t count, void *pool
     b->pool[0] = pool_a;
     b->pool[1] = pool_b;
     b->bytes_each = bytes_each;
-    // row layout: 256 threads (64-cavity mix, FP32: 638 us per step, 673 at 512; FP16, bound by
-    // arithmetic, 397 at 512)
-    b->cfg.bx = b->rows && b->storage != CLBM_F16_DEV ? 256 : max_threads(b);
     b->cfg.by = 1;
     b->cfg.blocks_per_cu = 1024;    // capped at one item per wave (row layout) or one tile per workgroup
     b->cfg.graph_steps = 20;
@@ -493,6 +490,13 @@ clbm_status clbm_batch_create(const clbm_params *inst, int32_t count, void *pool
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
         b->num_cus = cus;
+    // row layout: 256 threads (64-cavity mix, FP32: 647 us per step, 680 at 512; FP16, bound by
+    // arithmetic, 404 at 512), while the largest grid then gives each wave one item (2^20 items
+    // on 256 CUs): 32 cavities of edge 150, FP32, 1.7 M items: 3981 us per step at 256, 3329 at 512
+    uint64_t items = 0;
+    for (const Geom &g : b->geom) items += ((uint64_t)g.n + 63u) / 64u;
+    const bool covered = items <= (uint64_t)b->cfg.blocks_per_cu * b->num_cus * (256u / 64u);
+    b->cfg.bx = b->rows && b->storage != CLBM_F16_DEV && covered ? 256 : max_threads(b);
     b->cache_path = tune_cache_path ? tune_cache_path : "";
     b->cache_key = make_cache_key(b);
     clbm_batch_config cached;
