@@ -393,7 +393,8 @@ clbm_status clbm_batch_size(const clbm_params *inst, int32_t count, size_t *byte
  * instance index in the message); allocates the instance descriptors, the
  * tile table and reduction scratch; reads the tuned launch configuration
  * from tune_cache_path (nullable) when it holds an entry for exactly this set
- * of instances. */
+ * of instances in this layout, tuned on the present kernels (entries that
+ * earlier versions tuned stay in the file and are passed over). */
 clbm_status clbm_batch_create(const clbm_params *inst, int32_t count, void *pool_a, void *pool_b,
                               size_t bytes_each, const char *tune_cache_path, clbm_batch **out);
 

@@ -361,8 +361,15 @@ clbm_status build_graph(clbm_batch *b, int parity) {
     return CLBM_OK;
 }
 
+// Generation of the batch kernels in the tune cache's keys: entries tuned on
+// others (1: items per run of a row, packed passes) do not apply.  To be raised
+// when the kernels or the meaning of a configuration field change.
+constexpr int32_t kTuneGeneration = 2;
+
 std::string make_cache_key(const clbm_batch *b) {
     uint64_t h = 1469598103934665603ull;
+    const int32_t kernels[2] = {kTuneGeneration, b->rows ? 1 : 0};
+    h = fnv1a(h, kernels, sizeof(kernels));
     h = fnv1a(h, &b->storage, sizeof(b->storage));
     h = fnv1a(h, &b->route, sizeof(b->route));
     h = fnv1a(h, &b->count, sizeof(b->count));

@@ -38,3 +38,42 @@ def test_default_grid_gives_each_wave_one_item(clbm, count):
     ref = lat.populations()
     lat.close()
     assert torch.equal(first, ref) and torch.equal(last, ref)
+
+
+def _fnv1a(h, data):
+    for c in data:
+        h = ((h ^ c) * 1099511628211) & (2 ** 64 - 1)
+    return h
+
+
+def test_tune_cache_entries_apply_to_their_own_kernels(clbm, tmp_path):
+    """An entry applies to the layout it was tuned for; entries with the keys of
+    earlier kernels (storage, collision form and sizes alone) are passed over."""
+    import struct
+    specs = [W.cavity(12, 0.05, 0.8, 100.0), W.cavity(17, 0.05, 1.2, 100.0)]
+    cache = tmp_path / "tune.txt"
+    print("[gpu] tune cache keys", flush=True)
+
+    def config(layout, path=None):
+        b = clbm.Batch(specs, storage="f32", layout=layout, tune_cache=path)
+        cfg = b.get_config()
+        b.close()
+        return cfg
+
+    b = clbm.Batch(specs, storage="f32", layout="planes", tune_cache=str(cache))
+    b.init_rest()
+    b.autotune()
+    b.close()
+    key = cache.read_text().split()[0]
+    entry = "64 1 7 3 1 0"
+    tuned = dict(bx=64, by=1, blocks_per_cu=7, graph_steps=3, nt_stores=1, passes=0)
+    cache.write_text(f"{key} {entry}\n")
+    assert config("planes", str(cache)) == tuned
+    assert config("rows", str(cache)) == config("rows")
+    h = _fnv1a(1469598103934665603, struct.pack("<iii", clbm.STORAGE["f32"], 0, len(specs)))
+    for s in specs:
+        h = _fnv1a(h, struct.pack("<iii", s.nx, s.ny, s.nz))
+    old = key.rsplit("-", 1)[0] + f"-{h:016x}"
+    cache.write_text(f"{old} {entry}\n")
+    for layout in ("rows", "planes"):
+        assert config(layout, str(cache)) == config(layout)
