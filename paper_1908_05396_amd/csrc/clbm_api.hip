@@ -530,9 +530,13 @@ clbm_status clbm_autotune(clbm_lattice *h, void *stream, clbm_launch *best, doub
     hipStream_t st = (hipStream_t)stream;
     const int maxt = h->prm.storage == CLBM_F64 ? 256 : 512;
     const int wmax = (h->prm.nx + 63) / 64 * 64;
-    // candidates: one step per launch over block shapes, tile orders and cache
-    // hints, plus the two-step configuration in place if there is one
+    // candidates: the configuration in place and, while the library chooses, its
+    // own two-step launch (their workgroups and z chunks lie between those of the
+    // sweeps), then one step per launch over block shapes, tile orders and cache
+    // hints
     std::vector<StepLaunch> cands;
+    cands.push_back(h->launch);
+    if (h->pair_steps) cands.push_back(h->pair);
     for (int bx = 64; bx <= 512 && (bx <= wmax || bx == 64); bx *= 2)
         for (int by = 1; by <= 4; by *= 2) {
             if (bx * by > maxt || (by > 1 && by > h->prm.ny)) continue;
@@ -563,8 +567,6 @@ clbm_status clbm_autotune(clbm_lattice *h, void *stream, clbm_launch *best, doub
                     cands.push_back(c);
                 }
         }
-    if (h->launch.fuse_steps == 2)      // the two-step configuration in place
-        cands.push_back(h->launch);
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0), "autotune: event");
     hipError_t e = hipEventCreate(&e1);

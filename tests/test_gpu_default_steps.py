@@ -113,3 +113,31 @@ def test_results_do_not_depend_on_the_split(clbm, shape, periodic, lid):
         outs.append(lat.state_view().clone())
         lat.close()
     assert torch.equal(outs[0], outs[2]) and torch.equal(outs[1], outs[2])
+
+
+def _launches(fn, tmp_path):
+    """{(kernel, workgroups, threads)} of the step kernels that fn launches."""
+    import json
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    path = tmp_path / "trace.json"
+    prof.export_chrome_trace(str(path))
+    events = json.loads(path.read_text())["traceEvents"]
+    return {(e["name"], e["args"]["grid"][0], e["args"]["block"][0]) for e in events
+            if e.get("cat") == "kernel" and "stream_collide" in e["name"]}
+
+
+@pytest.mark.parametrize("shape,storage,steps", [((201, 191, 221), "f32", 4), ((201, 191, 221), "f32", 1),
+                                                 ((300, 440, 440), "f32", 1), ((70, 50, 40), "f64", 1)])
+def test_autotune_tries_the_default(clbm, tmp_path, shape, storage, steps):
+    """The launches that steps take by default are among those that the tuner
+    times: its choice is no worse than leaving it uncalled."""
+    print(f"[gpu] autotune {shape} {storage}", flush=True)
+    lat = clbm.Lattice(_box(*shape), storage=storage, track_residual=False)
+    lat.init_rest()
+    default = _launches(lambda: lat.step(steps), tmp_path)
+    tried = _launches(lat.autotune, tmp_path)
+    lat.close()
+    assert len(default) == 1 and default <= tried
