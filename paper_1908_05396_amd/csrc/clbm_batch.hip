@@ -633,14 +633,7 @@ clbm_status clbm_batch_step_each(clbm_batch *b, int64_t nsteps, void *stream) {
     for (; nsteps > 0; --nsteps) {
         for (int i = 0; i < b->count; ++i) {
             StepLaunch c;
-            const int nx = b->geom[i].nx;
-            c.bx = nx >= 256 ? 256 : (nx >= 64 ? 64 * (nx / 64) : nx);
-            if (c.bx > 256) c.bx = 256;
-            c.by = 1;
-            while (c.bx * c.by * 2 <= 256 && c.by * 2 <= b->geom[i].ny) c.by *= 2;
-            c.xcd_remap = 0;
-            c.nt_loads = 0;
-            c.nt_stores = 1;
+            default_launch(&b->prm[i], state_bytes_of(&b->prm[i]), &c);
             c.fuse_steps = 1;
             c.fuse_rows = 8;
             c.fuse_planes = 1;
@@ -648,7 +641,6 @@ clbm_status clbm_batch_step_each(clbm_batch *b, int64_t nsteps, void *stream) {
             Relax<float> pf = b->rf[i];
             pd.step = pf.step = (uint32_t)(b->steps_done + 1);
             if (b->rows) {
-                if (nx >= 64) c.by = 1;         // one lattice row per block, as for a single lattice
                 HIP_TRY(launch_step_rows(b->storage, storage_ptr(b, b->cur, i), (void *)storage_ptr(b, 1 - b->cur, i),
                                          b->geom[i], pd, pf, b->forced[i], b->route, c, st),
                         "clbm_batch_step_each");

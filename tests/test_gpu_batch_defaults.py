@@ -77,3 +77,33 @@ def test_tune_cache_entries_apply_to_their_own_kernels(clbm, tmp_path):
     cache.write_text(f"{old} {entry}\n")
     for layout in ("rows", "planes"):
         assert config(layout, str(cache)) == config(layout)
+
+
+@pytest.mark.parametrize("layout", ["rows", "planes"])
+@pytest.mark.parametrize("storage,L", [("f32", 48), ("f16", 50), ("f64", 96)])
+def test_step_each_launches_what_a_lattice_does(clbm, tmp_path, storage, L, layout):
+    """One launch per instance: the kernel, workgroups and store hint that the
+    instance takes as a lattice of its own (kernels read from a trace)."""
+    import json
+    from torch.profiler import ProfilerActivity, profile
+    spec = W.cavity(L, 0.05, 0.8, 100.0)
+    print(f"[gpu] step_each {storage} {layout} {L}", flush=True)
+
+    def launches(fn):
+        with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+            fn()
+            torch.cuda.synchronize()
+        path = tmp_path / "trace.json"
+        prof.export_chrome_trace(str(path))
+        return {(e["name"], e["args"]["grid"][0], tuple(e["args"]["block"]))
+                for e in json.loads(path.read_text())["traceEvents"]
+                if e.get("cat") == "kernel" and "stream_collide" in e["name"]}
+
+    b = clbm.Batch([spec], storage=storage, layout=layout)
+    lat = clbm.Lattice(spec, storage=storage, layout=layout, track_residual=False)
+    for x in (b, lat):
+        x.init_rest()
+    each, one = launches(lambda: b.step_each(1)), launches(lambda: lat.step(1))
+    b.close()
+    lat.close()
+    assert each == one and len(one) == 1
