@@ -259,12 +259,14 @@ stream_collide2_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax
     };
 
     // I(m) into LDS ring slots (index jm = m - z0 + 1) and the given registers
-    // (Only Pipe carries its values from one plane to the next: shared by the
-    // other forms they cost the planes layout 1-5%, 200 x 190 x 220 FP32 with 8
-    // rows 314 against 308 us per step, 100 x 90 x 80 79 against 75)
+    // (Pipe carries its values from one plane to the next.  Shared by the other
+    // forms too, that array changes their registers: 200 x 190 x 220 planes, 8
+    // rows, FP32 314 against 308 us per step with an array per plane, but FP16
+    // 304 against 326, forced 326 against 481 - 128 and 129 registers)
+    constexpr bool kCarried = Pipe || (!Rows && std::is_same<S, __half>::value);
     auto first_step = [&](int m, int jm, T (&loaded)[Q], T (&o0)[3], T (&op)[3], T (&om)[3]) {
         T gathered[Q];
-        T (&d)[Q] = Pipe ? loaded : gathered;
+        T (&d)[Q] = kCarried ? loaded : gathered;
         // The buffer descriptors of the 19 planes are rebuilt from the base
         // pointer on every plane instead of being kept (and spilled) across
         // the loop: the empty asm hides the pointer's loop invariance.
@@ -373,7 +375,7 @@ stream_collide2_kernel(const S *__restrict__ A, S *__restrict__ B, Geom g, Relax
 
     // plane m = z0 - 1 .. z1: first step of I(m), then the output plane m - 1
     T d[Q];
-    if constexpr (Pipe) {
+    if constexpr (kCarried) {
 #pragma unroll
         for (int a = 0; a < Q; ++a) d[a] = T(0);
     }
