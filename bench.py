@@ -12,8 +12,7 @@ of the main run's spin-up are timed on their own and reported as a secondary
 figure.  Each storage type runs in its faster launch form: FP32 two steps per
 launch (temporal blocking in the row-interleaved layout; one launch = two
 full steps of the fused pull stream-collide), FP16 deviations (stochastic rounding) and FP64
-one step per launch in the row-interleaved layout (a launch for the rows off
-the y and z faces and one for the face rows).  All storage types run the same
+one step per launch in the row-interleaved layout.  All storage types run the same
 spin-up, warm-up and timed steps, and the errors of FP32 and FP16 against FP64
 are reported on the centrelines u_x(y), u_y(x) and normwise over the whole
 field.
@@ -26,7 +25,7 @@ stream, with the measured HBM traffic of the committed counter summary
 beside it), the other launch form and the planes layout of each storage
 type, the FP16-deviation and FP64 storage variants of the same workload, the
 64-cavity batch (one graph-replayed launch per step vs one launch per
-instance, with its roofline), the achievable copy bandwidth, and the CPU
+instance in the library's default form, with its roofline), the achievable copy bandwidth, and the CPU
 oracle timed on the host cores on a bounded sample of the same workload.
 """
 
@@ -111,7 +110,7 @@ def accuracy_vs(torch, runs, ref_key, U, L):
 # Two steps per launch for each storage type: the fastest layout, patch
 # height, z chunk, tile order and store hint of a sweep at 512^3 (rows
 # 8/12/16 x planes 4..48 x both orders x both hints x both layouts).  FP32 in
-# the row layout with 16-plane chunks: 3.156 ms per step against 3.238 in the
+# the row layout with 16-plane chunks: 2.98 ms per step against 3.24 in the
 # planes layout with 32-plane chunks, the better one there.
 TWO_STEP = {"f32": {"fuse_steps": 2, "fuse_rows": 16, "fuse_planes": 16, "xcd_remap": 1, "nt_stores": 0},
             "f16": {"fuse_steps": 2, "fuse_rows": 16, "fuse_planes": 16, "xcd_remap": 1, "nt_stores": 0},

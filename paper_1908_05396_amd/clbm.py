@@ -238,7 +238,8 @@ class Lattice:
                  in_place: bool = False, layout: str = None, flags: torch.Tensor = None,
                  f16_rounding: str = "stochastic"):
         """layout: "rows" or "planes"; None picks planes for two steps per
-        launch (which need them), rows otherwise.  flags: optional uint8
+        launch, rows otherwise (either layout runs both forms; FP32 two-step
+        launches are faster in rows).  flags: optional uint8
         tensor of shape (nz, ny, nx) with CLBM_FLUID / CLBM_WALL /
         CLBM_MOVING_WALL per node (kept on the device for the lattice's
         lifetime)."""

@@ -51,7 +51,7 @@ static void set_step(clbm_lattice *h, int64_t step) {
     h->rd.step = h->rf.step = (uint32_t)step;
 }
 
-// Whether pairs of steps run faster as one two-step launch, and its z chunk.
+// Whether pairs of steps run faster as two-step launches, and their z chunk.
 //
 // The two-step kernel halves the state traffic but takes whole 62 x 14 column
 // patches and recomputes their rims, so it gains where the patches of the
@@ -59,9 +59,10 @@ static void set_step(clbm_lattice *h, int64_t step) {
 // c planes takes (c + 2) plane steps of 7.1 us (256^3) to 7.9 us (512^3).
 // Against it, one step per launch moves 152 bytes per node at 5.65 TB/s (rows of
 // whole 64-byte pieces), 5.0 TB/s (others) or 6.8 TB/s (both states within the
-// last-level cache).  Measured, FP32, us per step: 256^3 382 against 450,
-// 300 x 280 x 290 558 against 733, 200 x 190 x 220 224 against 250, 160^3 104
-// against 110; not taken at 192^3 (195 against 189) and 128^3 (66 against 58).
+// last-level cache).  Measured, FP32, us per step: 256^3 385 against 452,
+// 300 x 280 x 290 541 against 766, 200 x 190 x 220 229 against 252, 160^3 108
+// against 111; not taken at 192^3 (198 against 190) and 128^3 (95 against 58).
+// Near the line it errs by up to 3% (2000 x 30 x 100 161 against 157).
 // Chunks beyond 16 planes lose the cache lines that neighbouring patches share
 // (512^3: 2.98 ms at 16, 3.06 at 32).  FP16 and FP64 lose (bound by arithmetic),
 // the forced kernel spills registers, a periodic z axis is not pipelined.

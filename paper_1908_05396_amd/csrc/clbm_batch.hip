@@ -76,10 +76,11 @@ batch_step_kernel(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T>
 // the full wall rule by address selects as in the single-lattice flat kernel:
 // no idle lanes but in an instance's last item, and no separate faces.
 //
-// Bound: HBM and issue.  64 cavities of edge 32 to 96, FP32: 638 us per
-// step, 5.1 TB/s (682 with an item per run of a row, the short tails of two
-// rows sharing a wave: 1.19 lanes per node and a second round of loads for the
-// x faces).
+// Bound: HBM through the vector memory pipe.  64 cavities of edge 32 to 96,
+// FP32: 647 us per step, 5.3 TB/s moved at 1.03 times the bytes needed (692 with
+// an item per run of a row, the short tails of two rows sharing a wave: 1.19
+// lanes per node and a second round of loads for the x faces); waves stand ready
+// but not issued 73% of their time with the VALU 36% busy.
 template <typename S, typename T, int Route, int StAux, bool AnyForced>
 __device__ __forceinline__ void batch_nodes(const S *__restrict__ A, S *__restrict__ B, const BatchInst<T> &in, uint32_t n,
                                    uint32_t step) {
@@ -440,11 +441,12 @@ clbm_status clbm_batch_size(const clbm_params *inst, int32_t count, size_t *byte
         if (inst[i].collision == CLBM_COLLIDE_SRT)
             return fail(CLBM_EINVAL, "instance %d: batches run the cascaded scheme only", i);
         if (inst[i].layout != inst[0].layout) return fail(CLBM_EINVAL, "instance %d: layout differs", i);
-        // the row of a node within its layer comes from a float estimate with
-        // one correction, exact while a layer has at most 2^22 nodes
+        // planes: the row of a node within its layer comes from a float estimate
+        // with one correction, exact while a layer has at most 2^22 nodes; rows:
+        // the same limit, so that both layouts take the same instances
         if ((int64_t)inst[i].nx * inst[i].ny > ((int64_t)1 << 22))
             return fail(CLBM_EINVAL, "instance %d: a z layer of more than 2^22 nodes", i);
-        // row layout: packed items address an instance's state with 32-bit signed byte offsets
+        // row layout: 32-bit byte offsets, a layer's lead included, reach the whole instance
         if (inst[i].layout == CLBM_LAYOUT_ROWS && state_bytes_of(&inst[i]) >= ((size_t)1 << 31) - ((size_t)1 << 24))
             return fail(CLBM_EINVAL, "instance %d: a state of 2 GiB or more in a row-layout batch", i);
         total += instance_bytes(&inst[i]);
@@ -750,7 +752,7 @@ clbm_status clbm_batch_autotune(clbm_batch *b, void *stream, clbm_batch_config *
     HIP_TRY(hipEventCreate(&e0), "autotune: event");
     HIP_TRY(hipEventCreate(&e1), "autotune: event");
     clbm_status result = CLBM_OK;
-    static const int packings[] = {0, 2, 4, 8};     // row layout: one row run per item, or packed passes
+    static const int packings[] = {0, 2, 4, 8};     // row layout: groups of 64 nodes per item (0: one)
     for (const auto &sh : shapes)
     for (int pk : packings) {
         clbm_batch_config c = keep;

@@ -151,8 +151,9 @@ aa_even_flat_kernel(S *__restrict__ A, Geom g, Relax<T> p, FlatGrid L) {
 // source of b = opp(a), so the store of a goes to exactly the address that
 // direction b was loaded from.
 //
-// Bound: HBM, whose rate the pair of misaligned reads and writes keeps below the
-// two-buffer step's: 250 x 240 x 230 FP32 414 us per step, 5.1 TB/s (510 with
+// Bound: HBM through the vector memory pipe: 1.06 and 1.03 times the bytes
+// needed are read and written, waves stand ready but not issued 69% of their
+// time with the VALU 42% busy.  250 x 240 x 230 FP32 418 us per step, 5.0 TB/s (510 with
 // one wave per run of a row, the x faces apart and the y and z faces in a second
 // launch with a wait per direction).
 template <typename S, typename T, bool Forced, int Route, bool Far>
